@@ -153,7 +153,7 @@ def _prepare_cascade(case, seed):
     first = 0
     for k, m in (("el", n), ("po", npo)):
         x = _uniform(gen, 3 * m, 0.0, TWO_PI, torch.float32).view(3, m)
-        p = 10.0 * torch.randn(3, m, generator=gen, device="cuda")
+        p = 200.0 * torch.randn(3, m, generator=gen, device="cuda")     # gamma of some hundreds, as the cascade goes on
         _fill(src[k], x, p, torch.arange(first, first + m, device="cuda"))
         first += m
     del x, p
