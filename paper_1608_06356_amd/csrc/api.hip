@@ -258,15 +258,13 @@ int qed_build_tables_range(qed_ctx_t c, int formula, double rad_chi_max, double 
     return fail(c, QED_ERR_ARG, "build_tables_range: need 1 <= rad_chi_max <= 1e6 and 10 <= pair_chi_max <= 1e6");
   hipError_t e = hipSuccess;
   if (!c->rad_lnh64) {
-    const size_t work = (size_t)(kRadNChi + kPairNRate + kPairNCdf) * (4 * 1024 + 1);
     if ((e = dalloc(&c->rad_lnh64, kRadNChi)) != hipSuccess || (e = dalloc(&c->rad_S64, kRadNChi * kNU)) != hipSuccess ||
         (e = dalloc(&c->rad_lnh32, kRadNChi)) != hipSuccess || (e = dalloc(&c->rad_s0sc, 2 * kRadNChi)) != hipSuccess ||
         (e = dalloc(&c->rad_q16, kRadNChi * kNU)) != hipSuccess || (e = dalloc(&c->pair_L64, kPairNRate)) != hipSuccess ||
         (e = dalloc(&c->pair_S64, kPairNCdf * kNU)) != hipSuccess || (e = dalloc(&c->pair_L32, kPairNRate)) != hipSuccess ||
         (e = dalloc(&c->pair_s0sc, 2 * kPairNCdf)) != hipSuccess || (e = dalloc(&c->pair_q16, kPairNCdf * kNU)) != hipSuccess ||
-        (e = dalloc(&c->rad_chk, kRadNChi * 82)) != hipSuccess || (e = dalloc(&c->tab_work, work)) != hipSuccess)
+        (e = dalloc(&c->rad_chk, kRadNChi * 82)) != hipSuccess || (e = dalloc(&c->tab_work, kTabWork)) != hipSuccess)
       return hip_fail(c, e, "build_tables: hipMalloc");
-    c->tab_work_elems = work;
   }
   c->tables_ready = false;
   const TabRange rg = make_range(rad_chi_max, pair_chi_max);

@@ -20,6 +20,9 @@ constexpr int64_t kCompactTile = 1024;
 // Largest node count per side of qed_fill_standing_wave grids.
 constexpr int kMaxWaveGrid = 4096;
 
+// Coefficients the table builder keeps: 333 intervals, 7 functions, 10 terms.
+constexpr size_t kTabWork = (size_t)333 * 7 * 10;
+
 struct qed_ctx {
   int device = 0;
   qed_params_t params{};
@@ -36,8 +39,7 @@ struct qed_ctx {
   float *pair_L32 = nullptr, *pair_s0sc = nullptr;       // [512], [2*256]
   uint16_t *pair_q16 = nullptr;
   float *rad_chk = nullptr;                              // [256 * 82] Hermite CDF check rows
-  double *tab_work = nullptr;                            // quadrature scratch
-  size_t tab_work_elems = 0;
+  double *tab_work = nullptr;                            // series of the quadrature's functions [kTabWork]
 
   // counters and ids
   unsigned long long *d_counters = nullptr;              // qed_counters_t layout

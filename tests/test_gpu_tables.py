@@ -92,3 +92,26 @@ def test_wide_range_tables_vs_oracle():
     with pytest.raises(q.QEDError):
         ctx.qed_build_tables_range(q.QED_FORMULA_I, 1e7, 1e5)
     ctx.close()
+
+
+@pytest.mark.parametrize("formula,lnh_tol,s_tol", [("I", 1e-11, 1e-8), ("II", 1e-10, 1e-7)])
+@pytest.mark.parametrize("rad_hi,pair_hi", [(1.0, 10.0), (1e6, 1e6)])
+def test_tables_at_the_ends_of_the_range(formula, lnh_tol, s_tol, rad_hi, pair_hi):
+    """Smallest and largest chi ranges, where the arguments of the interpolated
+    functions reach the ends of their intervals: sampled rows against the
+    oracle's quadrature (of Eq. 1, the same function as Eq. 4), with the bars of
+    the default range."""
+    torch, q = need_gpu()
+    ctx = q.Context()
+    ctx.qed_build_tables_range({"I": q.QED_FORMULA_I, "II": q.QED_FORMULA_II}[formula], rad_hi, pair_hi)
+    lnh, S, L, PS = (ctx.qed_get_table(w) for w in range(4))
+    ref = tables.build_rad_table("I", rows=[0, 1, 255], chi_max=rad_hi)
+    pref = tables.build_pair_table(rate_rows=[0, 1, 511], cdf_rows=[0, 255], chi_max=pair_hi)
+    for i in (0, 1, 255):
+        assert abs(lnh[i] - ref.ln_h[i]) < lnh_tol
+        assert np.abs(S[i] - ref.s[i]).max() < s_tol
+    for i in (0, 1, 511):
+        assert abs(L[i] - pref.L[i]) < 1e-10
+    for i in (0, 255):
+        assert np.abs(PS[i] - pref.s[i]).max() < 1e-8
+    ctx.close()
