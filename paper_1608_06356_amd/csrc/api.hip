@@ -569,7 +569,7 @@ int qed_surrogate_grad(qed_ctx_t c, int net, const float *x, const float *t, con
                        float *grad, void *st) {
   if (!c || !x || !t || !grad || n < 1 || (net != 0 && net != 1)) return QED_ERR_ARG;
   if (!c->mlp_theta[net]) return fail(c, QED_ERR_STATE, "surrogate weights not set");
-  hipError_t e = hipMemsetAsync(grad, 0, qed::mlp_params(net) * sizeof(float), S(st));
+  hipError_t e = qed::launch_zero(grad, qed::mlp_params(net), S(st));
   if (e == hipSuccess)
     e = qed::launch_mlp_grad(net, c->mlp_theta[net], grad, nullptr, nullptr, nullptr, x, t, mask, n, 0, 0, S(st));
   return e == hipSuccess ? QED_OK : hip_fail(c, e, "surrogate_grad");

@@ -115,6 +115,7 @@ hipError_t launch_mlp_init(float *theta, int net, uint32_t seed, hipStream_t st)
 hipError_t launch_mlp_grad(int net, const float *theta, float *grad, const double *S64, const double *lnh,
                            const double *L, const float *ext_x, const float *ext_t, const float *ext_m,
                            int64_t nbatch, uint64_t sample0, uint32_t seed, hipStream_t st);
+hipError_t launch_zero(float *p, int n, hipStream_t st);
 hipError_t launch_adam(float *theta, float *grad, float *m, float *v, int net, float lr, float b1t, float b2t,
                        hipStream_t st);
 hipError_t launch_mlp_forward(const float *theta, int net, const float *x, int64_t n, float *y, hipStream_t st);

@@ -1,8 +1,7 @@
 // Device building blocks of the surrogate networks (shared by the training and
 // sampling kernels in mlp.hip and the surrogate variants of the step kernels):
-// split-BF16 64x64 layers on the K = 16 (training) and K = 32 (inference) bf16
-// matrix instructions, the 16-sample forward passes, the input normalisation and
-// the residual-check CDF rows.
+// split-BF16 64x64 layers on the K = 32 bf16 matrix instruction, the 16-sample
+// forward pass, the input normalisation and the residual-check CDF rows.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -55,125 +54,18 @@ __device__ __forceinline__ void split1(float x, uint16_t &hi, uint16_t &lo) {
 }
 __device__ __forceinline__ float sigm(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 __device__ __forceinline__ float silu(float z) { return z * sigm(z); }
-__device__ __forceinline__ float dsilu(float z) {
-  const float s = sigm(z);
-  return s * (1.0f + z * (1.0f - s));
-}
-
-// Weights of one net staged in LDS: split 64x64 layers, optionally their
-// transposes, and the float32 small layers.  A 64x64 layer is stored in the
-// order the matrix-core A operand is read: the 16x16 block (mt, ks) holds, for
-// lane L, the four elements (row mt*16 + L%16, columns ks*16 + 4*(L/16) .. +3)
-// at ((mt*4 + ks)*64 + L)*4, so that a wave reads 512 contiguous bytes per
-// block (row-major rows of 128 B put 16 lanes on the same LDS banks).
-__host__ __device__ constexpr int swz(int r, int c) {
-  return (((r >> 4) * 4 + (c >> 4)) * 64 + (r & 15) + 16 * ((c & 15) >> 2)) * 4 + (c & 3);
-}
-
-struct NetLds {
-  uint16_t W2h[H * H], W2l[H * H], W3h[H * H], W3l[H * H];
-  float W1[H * 2], b1[H], b2[H], b3[H], W4[2 * H], b4[2];
-};
-struct NetLdsT {
-  uint16_t W2h[H * H], W2l[H * H], W3h[H * H], W3l[H * H];   // transposed
-};
-
-__device__ void stage_net(const float *th, const Layout &L, NetLds *s, NetLdsT *t) {
-  for (int k = threadIdx.x; k < H * H; k += blockDim.x) {
-    const int r = k / H, c = k % H, sk = swz(r, c), tk = swz(c, r);
-    uint16_t h, l;
-    split1(th[L.W2 + k], h, l);
-    s->W2h[sk] = h; s->W2l[sk] = l;
-    if (t) { t->W2h[tk] = h; t->W2l[tk] = l; }
-    split1(th[L.W3 + k], h, l);
-    s->W3h[sk] = h; s->W3l[sk] = l;
-    if (t) { t->W3h[tk] = h; t->W3l[tk] = l; }
-  }
-  for (int k = threadIdx.x; k < H; k += blockDim.x) {
-    s->b1[k] = th[L.b1 + k]; s->b2[k] = th[L.b2 + k]; s->b3[k] = th[L.b3 + k];
-    for (int c = 0; c < L.nin; ++c) s->W1[k * L.nin + c] = th[L.W1 + k * L.nin + c];
-    for (int o = 0; o < L.nout; ++o) s->W4[o * H + k] = th[L.W4 + o * H + k];
-  }
-  if (threadIdx.x < L.nout) s->b4[threadIdx.x] = th[L.b4 + threadIdx.x];
-}
-
-// out = W a (64x64 layer, split products); a and out in the lane layout.
-__device__ __forceinline__ void mm64(const uint16_t *Wh, const uint16_t *Wl, const float a[4][4],
-                                     float out[4][4]) {
-  const int lane = threadIdx.x & 63;
-  s4 bh[4], bl[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) split4(a[ks], bh[ks], bl[ks]);
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int off = ((mt * 4 + ks) * 64 + lane) * 4;   // = swz(mt*16 + lane%16, ks*16 + 4*(lane/16))
-      const s4 ah = *reinterpret_cast<const s4 *>(Wh + off);
-      const s4 al = *reinterpret_cast<const s4 *>(Wl + off);
-      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh[ks], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bl[ks], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh[ks], acc, 0, 0, 0);
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) out[mt][v] = acc[v];
-  }
-}
-
 // Keeps LDS-resident weights from being hoisted into registers across tiles
 // (the loop-invariant loads of two nets would exceed the register file).
 __device__ __forceinline__ void reload_barrier() { asm volatile("" ::: "memory"); }
 
 __device__ __forceinline__ int feat(int mt, int v) { return mt * 16 + 4 * ((threadIdx.x & 63) >> 4) + v; }
 
-struct Cache {
-  float z1[4][4], z2[4][4], z3[4][4], a3[4][4];
-};
-
-// Forward pass of one 16-sample tile; x0, x1 are the inputs of this lane's sample.
-__device__ __forceinline__ void forward(const NetLds &s, int nin, int nout, float x0, float x1,
-                                        float y[2], Cache &c) {
-  float a[4][4], z[4][4];
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int f = feat(mt, v);
-      float t = s.b1[f] + s.W1[f * nin] * x0;
-      if (nin > 1) t += s.W1[f * nin + 1] * x1;
-      c.z1[mt][v] = t;
-      a[mt][v] = silu(t);
-    }
-  mm64(s.W2h, s.W2l, a, z);
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) { z[mt][v] += s.b2[feat(mt, v)]; c.z2[mt][v] = z[mt][v]; a[mt][v] = silu(z[mt][v]); }
-  mm64(s.W3h, s.W3l, a, z);
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) { z[mt][v] += s.b3[feat(mt, v)]; c.z3[mt][v] = z[mt][v]; c.a3[mt][v] = silu(z[mt][v]); }
-  for (int o = 0; o < nout; ++o) {
-    float p = 0.f;
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) p += s.W4[o * H + feat(mt, v)] * c.a3[mt][v];
-    p += __shfl_xor(p, 16, 64);
-    p += __shfl_xor(p, 32, 64);
-    y[o] = p + s.b4[o];
-  }
-}
-
 // ------------------------------------------------------------- inference
-// Every inference kernel uses forward_inf: it evaluates the same function as
-// `forward` (the same split products of the same activations) with fewer
-// instructions: the biases are the initial accumulators of the matrix products,
-// the small layers are read 16 bytes at a time, and the 64x64 products use the
-// K = 32 matrix-core instruction (half the instructions of K = 16).  Measured on
-// the lepton pass of the surrogate step: 1.21 -> 1.03 ms for 1e7 electrons.
+// Every inference kernel uses forward_inf: the biases are the initial accumulators
+// of the matrix products, the small layers are read 16 bytes at a time, and the
+// 64x64 products use the K = 32 matrix-core instruction (half the instructions of
+// K = 16).  Measured on the lepton pass of the surrogate step: 1.21 -> 1.03 ms for
+// 1e7 electrons.
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 
 // K = 32 layout of a 64x64 layer.  The order of k inside a 32-wide block is
@@ -187,8 +79,7 @@ __host__ __device__ constexpr int swz32(int r, int c) {
   return (((r >> 4) * 2 + (c >> 5)) * 64 + ((c & 15) >> 2) * 16 + (r & 15)) * 8 + ((c >> 4) & 1) * 4 + (c & 3);
 }
 
-// Inference copy of one net in LDS (distinct type: the 64x64 layers are in
-// the swz32 order, not the swz order of NetLds).
+// Inference copy of one net in LDS: the 64x64 layers split, in the swz32 order.
 struct alignas(16) NetLdsI {
   uint16_t W2h[H * H], W2l[H * H], W3h[H * H], W3l[H * H];
   float W1[H * 2], b1[H], b2[H], b3[H], W4[2 * H], b4[2];

@@ -71,6 +71,31 @@ def test_forward_and_gradient_vs_oracle(net, netid):
     assert np.all(gerr <= mlp_bound.K_SIGMA * sg)
 
 
+@pytest.mark.parametrize("net,netid", [("A", 0), ("B", 1)])
+@pytest.mark.parametrize("n", [1, 16, 17, 4096, 20011])
+def test_gradient_batch_sizes(net, netid, n):
+    """Gradient at batches of one sample, one tile, a tile and one sample, the
+    training batch (several tiles per workgroup), and five tiles per workgroup
+    with a ragged end, no mask: elementwise within the derived bound."""
+    torch, q = need_gpu()
+    ctx = q.Context()
+    th = _rand_theta(net, 30 + netid)
+    ctx.qed_surrogate_io(netid, th)
+    nin, nout = mlp.SIZES[net]
+    rng = np.random.default_rng(n)
+    X = rng.uniform(-1, 1, (n, nin)).astype(np.float32)
+    T = rng.normal(size=(n, nout)).astype(np.float32)
+    g = torch.full((mlp.n_params(net),), 7.0, dtype=torch.float32, device="cuda")
+    print(f"gradient of net {net}, {n} samples", flush=True)
+    ctx.qed_surrogate_grad(netid, torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda(), None, g)
+    torch.cuda.synchronize()
+    ge, bound = mlp_bound.grad_bound(th.astype(np.float64), net, X.T.astype(np.float64), T.T.astype(np.float64),
+                                     np.ones((nout, n)))
+    err = np.abs(g.cpu().numpy().astype(np.float64) - ge)
+    print(f"  max err/bound {np.max(err / bound):.3f}")
+    assert np.all(err <= bound)
+
+
 @pytest.fixture(scope="module")
 def trained():
     torch, q = need_gpu()
