@@ -67,23 +67,33 @@ void free_emitters(qed_ctx *c) {
 void free_scan(qed_ctx *c) {
   (void)hipFree(c->d_status);
   c->d_status = nullptr;
-  c->reserved = 0; c->status_len = 0;
+  c->reserved = 0;
 }
 
-// Scan state for species of up to n particles (one status word per tile of
-// the smallest tile size, 256).  Allocates, so not under graph capture.
+// Scan state for species of up to n particles (one status word per tile), clear.
+// Allocates, so not under graph capture.
 int ensure_scan(qed_ctx *c, int64_t n) {
   if (n <= c->reserved) return QED_OK;
   hipError_t e = hipDeviceSynchronize();
   if (e != hipSuccess) return hip_fail(c, e, "reserve");
   free_scan(c);
-  const int64_t status_len = n / 256 + 64;
-  if ((e = dalloc(&c->d_status, 2 * status_len)) != hipSuccess) {   // two regions (see qed_ctx)
+  // particles per tile of each region's user; up to 2^18 particles the float64
+  // pair pass, and up to 2^17 the emission, takes tiles of 256
+  const int64_t tile[kScanRegions] = {kCompactTile, 16384, 512, 512, 16384, 256};
+  int64_t words = 0;
+  for (int k = 0; k < kScanRegions; ++k) {
+    c->region_at[k] = words;
+    c->region_len[k] = n / tile[k] + 64 + (k == kRegEmit || k == kRegClean ? 2048 : 0);
+    words += c->region_len[k];
+  }
+  if ((e = dalloc(&c->d_status, words)) != hipSuccess ||
+      (e = hipMemset(c->d_status, 0, words * sizeof(uint64_t))) != hipSuccess ||
+      (e = hipMemset(c->d_ticket, 0, kScanRegions * sizeof(uint32_t))) != hipSuccess ||
+      (e = hipDeviceSynchronize()) != hipSuccess) {
     free_scan(c);
     return hip_fail(c, e, "reserve: hipMalloc");
   }
   c->reserved = n;
-  c->status_len = status_len;
   return QED_OK;
 }
 
@@ -130,6 +140,8 @@ int ensure_cands(qed_ctx *c, int64_t n) {
 }
 
 hipStream_t S(void *s) { return (hipStream_t)s; }
+
+constexpr int kCounterWords = qed::kCounterSlots * qed::cNumCounters;   // (see counter_slot)
 
 // ------------------------------------------- static scratch (qed_compact_static)
 // Scan state of qed_compact_static in a file-scope device array, so that the
@@ -180,14 +192,14 @@ int qed_create(qed_ctx_t *out, const qed_params_t *p) {
   if (e == hipSuccess) e = static_scratch_address(c->device, &c->static_scratch);
   if (e == hipSuccess) e = qed::mlp_set_attributes();
   if (e == hipSuccess) e = qed::step_set_attributes();
-  if (e == hipSuccess) e = dalloc(&c->d_counters, qed::cNumCounters);
+  if (e == hipSuccess) e = dalloc(&c->d_counters, kCounterWords);
   if (e == hipSuccess) e = dalloc(&c->d_next_id, 1);
   if (e == hipSuccess) e = dalloc(&c->d_n_emit, 1);
-  if (e == hipSuccess) e = dalloc(&c->d_ticket, 2);
+  if (e == hipSuccess) e = dalloc(&c->d_ticket, kScanRegions);
   if (e == hipSuccess) e = dalloc(&c->d_killed, 1);
   if (e == hipSuccess) e = dalloc(&c->d_step, 1);
   if (e == hipSuccess) e = hipMemset(c->d_step, 0, sizeof(int64_t));
-  if (e == hipSuccess) e = hipMemset(c->d_counters, 0, sizeof(unsigned long long) * qed::cNumCounters);
+  if (e == hipSuccess) e = hipMemset(c->d_counters, 0, sizeof(unsigned long long) * kCounterWords);
   if (e == hipSuccess) e = hipMemset(c->d_next_id, 0, sizeof(uint64_t));
   if (e == hipSuccess) e = hipMemset(c->d_n_emit, 0, sizeof(int64_t));
   if (e == hipSuccess) e = hipMemset(c->d_killed, 0, sizeof(int64_t));
@@ -579,13 +591,16 @@ static_assert(sizeof(qed_counters_t) == sizeof(int64_t) * qed::cNumCounters, "co
 
 int qed_get_status(qed_ctx_t c, qed_counters_t *out, void *st) {
   if (!c || !out) return QED_ERR_ARG;
-  unsigned long long h[qed::cNumCounters];
+  unsigned long long h[kCounterWords];
   hipError_t e = hipStreamSynchronize(S(st));
   if (e == hipSuccess) e = hipMemcpy(h, c->d_counters, sizeof(h), hipMemcpyDeviceToHost);
   if (e == hipSuccess) e = hipMemset(c->d_counters, 0, sizeof(h));
   if (e != hipSuccess) return hip_fail(c, e, "get_status");
   int64_t *o = (int64_t *)out;
-  for (int k = 0; k < qed::cNumCounters; ++k) o[k] = (int64_t)h[k];
+  for (int k = 0; k < qed::cNumCounters; ++k) {
+    o[k] = 0;
+    for (int j = 0; j < qed::kCounterSlots; ++j) o[k] += (int64_t)h[j * qed::cNumCounters + k];
+  }
   if (out->scan_timeouts) return fail(c, QED_ERR_STATE, "prefix scan timed out");
   if (out->dropped) return fail(c, QED_ERR_CAPACITY, "appends dropped: species capacity exceeded");
   return QED_OK;

@@ -23,6 +23,15 @@ constexpr int kMaxWaveGrid = 4096;
 // Coefficients the table builder keeps: 333 intervals, 7 functions, 10 terms.
 constexpr size_t kTabWork = (size_t)333 * 7 * 10;
 
+// Largest capacity of the emission without a list (tiles of 256 particles).
+constexpr int64_t kEmitSmall = (int64_t)1 << 17;
+
+// Uses of the scan state.  kRegClean: compaction and the float64 pair pass, whose
+// kernels leave it clear; the others are cleared by an earlier kernel of the same
+// call sequence: the emission's by qed_gather_push (its index's again by the first
+// surrogate pass), the float32 pair pass's by its streaming kernel.
+enum ScanRegion { kRegClean = 0, kRegEmitIndex, kRegEmit, kRegEmitCont, kRegPairIndex, kRegPairCand, kScanRegions };
+
 struct qed_ctx {
   int device = 0;
   qed_params_t params{};
@@ -73,12 +82,11 @@ struct qed_ctx {
   int64_t *d_killed = nullptr;
   const void *killed_owner = nullptr;
 
-  // decoupled look-back scan state: two tickets and two status regions of
-  // status_len words; region 1 serves the emitter index so that one launch can
-  // clear the state of both scans of qed_emit_photons
+  // decoupled look-back scan state: a ticket and a region of status words for each
+  // use (ScanRegion), all clear between calls
   uint32_t *d_ticket = nullptr;
   uint64_t *d_status = nullptr;
-  int64_t status_len = 0;
+  int64_t region_at[kScanRegions] = {}, region_len[kScanRegions] = {};
 
   int n_cu = 256;
 

@@ -36,7 +36,7 @@ __host__ __device__ inline TabRange make_range(double rad_hi, double pair_hi) {
 // ln and exp: Fast selects the hardware log2/exp2 instructions in float32
 // (relative error ~1e-6 after the change of base), for the rate of the push.
 template <typename R, bool Fast> struct Math {
-  static __device__ __forceinline__ R ln(R v) { return log(v); }
+  static __device__ __forceinline__ R ln(R v) { return ln_any(v); }
   static __device__ __forceinline__ R ex(R v) { return exp(v); }
 };
 template <> struct Math<float, true> {
@@ -137,7 +137,10 @@ struct RowQ16 {
 // Returns false in the low tail (t < t_lo), where the caller applies its tail law.
 template <typename R, typename Tab>
 __device__ __forceinline__ bool interp_s(const Tab &tab, int row, R u, double tlo, double tinv, R &s) {
-  const R t = log(u) - log1p(-u);
+  // (1 - u is exact for every draw, so in float64 the plain logarithm serves)
+  R t;
+  if constexpr (sizeof(R) == 8) t = ln_finite(u) - ln_finite((R)1 - u);
+  else t = log(u) - log1p(-u);
   const R y = (t - (R)tlo) * (R)tinv;
   if (y < (R)0) return false;
   if (y >= (R)(kNU - 1)) { s = (R)tab.at(row, kNU - 1); return true; }
@@ -154,7 +157,7 @@ __device__ __forceinline__ bool interp_s(const Tab &tab, int row, R u, double tl
 // u = 1e-4 the infrared law xi ~ u^3 continues the first node.
 template <typename R, typename Tab>
 __device__ __forceinline__ void sample_rad(const Tab &tab, R chi, R u, R u_row, R &xi, R &om, const TabRange &rg) {
-  const R lnchi = log(chi);
+  const R lnchi = ln_any(chi);
   const int row = pick_row<R>(lnchi, u_row, rg.rad_lnlo, rg.rad_inv);
   R s;
   if (interp_s<R>(tab, row, u, rg.rad_tlo, rg.rad_tinv, s)) {
@@ -176,7 +179,7 @@ __device__ __forceinline__ void sample_rad(const Tab &tab, R chi, R u, R u_row, 
 template <typename R, typename Tab>
 __device__ __forceinline__ void sample_pair_half(const Tab &tab, R chi, R u, R u_row, R &xi, R &om,
                                                  const TabRange &rg) {
-  const int row = pick_row<R>(log(chi), u_row, rg.pair_lnlo, rg.pair_cdf_inv);
+  const int row = pick_row<R>(ln_any(chi), u_row, rg.pair_lnlo, rg.pair_cdf_inv);
   R s;
   if (!interp_s<R>(tab, row, u, rg.pair_tlo, rg.pair_tinv, s)) s = (R)tab.at(row, 0);
   xi = (R)1 / ((R)1 + exp(-s));

@@ -506,8 +506,9 @@ __global__ __launch_bounds__(kInferThreads) void k_infer(InferArgs a) {
   // per-wave totals of fallbacks
   for (int o = 32; o > 0; o >>= 1) { nfx += __shfl_xor(nfx, o, 64); nfr += __shfl_xor(nfr, o, 64); }
   if (lane == 0) {
-    if (nfx) atomicAdd(&a.fallback[0], (unsigned long long)nfx);
-    if (nfr) atomicAdd(&a.fallback[1], (unsigned long long)nfr);
+    unsigned long long *f = a.fallback + (blockIdx.x % kCounterSlots) * cNumCounters;
+    if (nfx) atomicAdd(&f[0], (unsigned long long)nfx);
+    if (nfr) atomicAdd(&f[1], (unsigned long long)nfr);
   }
 }
 

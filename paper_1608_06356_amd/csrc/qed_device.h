@@ -45,6 +45,7 @@ enum Purpose : uint32_t { kInitTau = 0, kLeptonEvent = 1, kPhotonEvent = 2, kLep
 enum Counter { cEvents = 0, cPhotons, cRejected, cCapped, cPairs, cDropped, cChiRange,
                cNanChi, cScanTimeout, cCompacted, cMlpFallbackXi, cMlpFallbackRate, cThinned,
                cEnvelopeExceeded, cRetired, cBoxFallback, cNumCounters };
+constexpr int kCounterSlots = 64;              // copies of the counters (see counter_slot)
 
 // ------------------------------------------------------------------ Philox
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): 10 rounds of two 32x32->64
@@ -72,6 +73,52 @@ __device__ __forceinline__ uint4 stream4(uint64_t id, uint32_t seed, uint64_t st
 template <typename R> __device__ __forceinline__ R unit(uint32_t x) {
   return ((R)(x >> 9) + (R)0.5) * (R)1.1920928955078125e-07;
 }
+
+// Natural logarithm in float64 of a positive finite number.  x = 2^k (1 + f) with
+// 1 + f in [sqrt(1/2), sqrt(2)), f exact; with s = f / (2 + f), h = f^2 / 2 and
+// R = sum_k 2 s^(2k) / (2k + 1), ln(1 + f) = 2 atanh(s) = f - (h - s (h + R)); the
+// terms beyond the tenth stay below 2e-18 (|s| < 0.1716).  f and k ln 2 carry the
+// leading digits, so the error is below one unit in the last place.  About 40
+// instructions where the library's function, which works in pairs of float64,
+// takes 130: the event kernels are bound by the latency of such chains.
+__device__ __forceinline__ double ln_finite(double x) {
+  double m = __builtin_amdgcn_frexp_mant(x);              // [1/2, 1)
+  int k = __builtin_amdgcn_frexp_exp(x);
+  const bool low = m < 0.70710678118654752;
+  m = low ? 2.0 * m : m;
+  k -= low ? 1 : 0;
+  const double f = m - 1.0, d = 2.0 + f;
+  double y = __builtin_amdgcn_rcp(d);                     // refined by two Newton steps, then the quotient once
+  y = fma(y, fma(-d, y, 1.0), y);
+  y = fma(y, fma(-d, y, 1.0), y);
+  double s = f * y;
+  s = fma(fma(-d, s, f), y, s);
+  const double z = s * s, h = 0.5 * f * f;
+  double r = 2.0 / 21.0;
+  r = fma(r, z, 2.0 / 19.0);
+  r = fma(r, z, 2.0 / 17.0);
+  r = fma(r, z, 2.0 / 15.0);
+  r = fma(r, z, 2.0 / 13.0);
+  r = fma(r, z, 2.0 / 11.0);
+  r = fma(r, z, 2.0 / 9.0);
+  r = fma(r, z, 2.0 / 7.0);
+  r = fma(r, z, 2.0 / 5.0);
+  r = fma(r, z, 2.0 / 3.0);
+  // k ln 2 in two parts, the first exact for |k| < 2^11
+  constexpr double kLn2Hi = 0x1.62e42fefa38p-1, kLn2Lo = 0x1.ef35793c7673p-45;
+  const double kd = (double)k, t = kd * kLn2Hi, sum = t + f, e = f - (sum - t);   // t + f = sum + e
+  return sum - ((h - fma(s, fma(r, z, h), kd * kLn2Lo)) - e);
+}
+
+// The same with the logarithm's values at zero, infinity, below zero and for NaN.
+__device__ __forceinline__ double ln_any(double x) {
+  const double r = ln_finite(x);
+  return x > 0.0 ? (x < INFINITY ? r : x) : (x == 0.0 ? -INFINITY : NAN);
+}
+__device__ __forceinline__ float ln_any(float x) { return logf(x); }
+
+// Optical depth of a draw.
+__device__ __forceinline__ double draw_tau(uint32_t u) { return -ln_finite(unit<double>(u)); }
 
 // ---------------------------------------------------------------- chi
 // Eq. (2) rearranged without subtraction of nearly equal squares: with n = p/|p|,

@@ -49,6 +49,24 @@ struct ScanDev {
   uint64_t *status;
 };
 
+// Scan regions an earlier kernel of the same call sequence clears for a later
+// one: the first n[k] status words and the ticket of region k (a launch of its
+// own for that would cost as much as the short kernels around it: 2 to 5 us).
+struct ScanClear {
+  static constexpr int kMax = 3;
+  ScanDev r[kMax];
+  int64_t n[kMax];
+};
+
+__device__ __forceinline__ void scan_clear(const ScanClear &c) {
+  const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+#pragma unroll
+  for (int k = 0; k < ScanClear::kMax; ++k) {
+    if (i0 == 0 && c.n[k]) *c.r[k].ticket = 0;
+    for (int64_t i = i0; i < c.n[k]; i += step) c.r[k].status[i] = 0;
+  }
+}
+
 // --------------------------------------------------------------- fields
 // x in [-L, 2L) -> [0, L) (one period at most per step); selects, no branches
 template <typename R>
@@ -351,13 +369,11 @@ __device__ __forceinline__ bool fields_finite(const R F[6]) {
   return isfinite(F[0]) && isfinite(F[1]) && isfinite(F[2]) && isfinite(F[3]) && isfinite(F[4]) && isfinite(F[5]);
 }
 
-__device__ __forceinline__ void count_add(unsigned long long *c, int which, uint32_t v) {
-  // one atomic per wave
-  const uint32_t lane = threadIdx.x & 63;
-  uint32_t s = v;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  if (lane == 0 && s) atomicAdd(&c[which], (unsigned long long)s);
+// Event counters are kept in kCounterSlots copies of their own cache lines, block b
+// adding to copy b % kCounterSlots (atomics on one line follow each other at about
+// 10 ns); qed_get_status adds them up.
+__device__ __forceinline__ unsigned long long *counter_slot(unsigned long long *c) {
+  return c + (blockIdx.x % kCounterSlots) * cNumCounters;
 }
 
 // Sum over the 64 lanes of a wave with DPP moves: the row steps of
@@ -388,7 +404,8 @@ __device__ __forceinline__ void count_zero(uint32_t *c) {
 }
 __device__ __forceinline__ void count_flush(const uint32_t *c, unsigned long long *g) {
   __syncthreads();
-  if (threadIdx.x < cNumCounters && c[threadIdx.x]) atomicAdd(&g[threadIdx.x], (unsigned long long)c[threadIdx.x]);
+  if (threadIdx.x < cNumCounters && c[threadIdx.x])
+    atomicAdd(&counter_slot(g)[threadIdx.x], (unsigned long long)c[threadIdx.x]);
 }
 
 // Emitter records are packed per wave: the emitter of particle i keeps its record
@@ -402,8 +419,16 @@ __device__ __forceinline__ int64_t rec_slot(int64_t i, uint64_t bits) {
 // Adds the number of lanes of the wave with `set` (one atomic per wave).
 __device__ __forceinline__ void count_flags(unsigned long long *c, int which, bool set) {
   const uint32_t s = (uint32_t)__popcll(__ballot(set));
-  if ((threadIdx.x & 63) == 0 && s) atomicAdd(&c[which], (unsigned long long)s);
+  if ((threadIdx.x & 63) == 0 && s) atomicAdd(&counter_slot(c)[which], (unsigned long long)s);
 }
+
+// Tickets are drawn one after the other at one address (about 14 ns each), so the
+// kernels below draw no more than they need: the workgroups past the tiles present
+// leave without one, and where every tile has its own workgroup no one draws a
+// second (single_turn).  Before, 1024 workgroups drew two each whatever the work:
+// 17 of 30 us of an emission with 190 tiles.
+__device__ __forceinline__ bool idle_block(int64_t ntiles) { return (int64_t)blockIdx.x >= ntiles; }
+__device__ __forceinline__ bool single_turn(int64_t ntiles) { return ntiles <= (int64_t)gridDim.x; }
 
 // Workgroup: obtain a tile id from the ticket (thread 0) and broadcast.
 __device__ __forceinline__ uint32_t next_tile(uint32_t *ticket, uint32_t *lds) {
@@ -411,6 +436,33 @@ __device__ __forceinline__ uint32_t next_tile(uint32_t *ticket, uint32_t *lds) {
   if (threadIdx.x == 0) *lds = atomicAdd(ticket, 1u);
   __syncthreads();
   return *lds;
+}
+
+// The same for a scan state that its kernel leaves clean.  Every workgroup draws
+// tickets until one is past its last tile, and this wave's status words have
+// arrived before it draws the next, so the workgroup with the last ticket of all
+// (ntiles tiles and one past them for each workgroup that is not idle) finds every other done with the state and clears it.
+// `last`: what that workgroup's first thread does before.
+struct Nothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <typename F = Nothing>
+__device__ __forceinline__ uint32_t next_tile_clean(const ScanDev &sc, uint32_t *lds, int64_t ntiles, F last = F()) {
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __builtin_amdgcn_s_waitcnt(0);
+    *lds = atomicAdd(sc.ticket, 1u);
+  }
+  __syncthreads();
+  const uint32_t tile = *lds;
+  const int64_t wgs = ntiles < (int64_t)gridDim.x ? (ntiles > 0 ? ntiles : 1) : (int64_t)gridDim.x;
+  if ((int64_t)tile == ntiles + wgs - 1) {
+    if (threadIdx.x == 0) last();
+    __syncthreads();
+    for (int64_t i = threadIdx.x; i < ntiles; i += blockDim.x) sc.status[i] = 0;
+    if (threadIdx.x == 0) *sc.ticket = 0;
+  }
+  return tile;
 }
 
 // Exclusive device-wide offset of this workgroup's tile given its per-thread count.
@@ -562,6 +614,7 @@ struct GPArgs {
   uint64_t step;
   const int64_t *d_step;
   TabRange rg;
+  ScanClear clear;       // the emission's scan regions
 };
 
 constexpr double kSubstepW = 0.2;     // method I: W Dt / N <= 0.2
@@ -690,6 +743,7 @@ __global__ __launch_bounds__(kGPThreads, (gp_waves<R, FK, M1>())) void k_gather_
   // (the grid is sized by the capacity: blocks beyond the particles present
   // return, and they are the last ones dispatched)
   const int64_t n = *a.sp.count;
+  scan_clear(a.clear);
   const int64_t base = gp_tile_base(kGPThreads);
   if (base >= n) return;
   const int t = threadIdx.x;
@@ -717,7 +771,7 @@ __global__ __launch_bounds__(kGPThreads, (gp_waves<R, FK, M1>())) void k_gather_
       if (live) gather_box<R>(box_s, rel[0], pit, w, F);
     } else {
       if (live) gather_global<R>(f, j[0], w, F);
-      if (threadIdx.x == 0) atomicAdd(&a.counters[cBoxFallback], 1ull);
+      if (threadIdx.x == 0) atomicAdd(&counter_slot(a.counters)[cBoxFallback], 1ull);
     }
   } else {
     __syncthreads();
@@ -740,6 +794,7 @@ __global__ __launch_bounds__(kGPThreads, kGPWaves) void k_gather_push2(GPArgs<fl
   __shared__ R lnh_s[kRadNChi];
   __shared__ BoxLds box_s;
   const int64_t n = *a.sp.count;
+  scan_clear(a.clear);
   const int64_t base = gp_tile_base((int64_t)kGPThreads * IT);
   if (base >= n) return;
   const int t = threadIdx.x;
@@ -764,7 +819,7 @@ __global__ __launch_bounds__(kGPThreads, kGPWaves) void k_gather_push2(GPArgs<fl
     tsc_setup<R>(f, xs[it][0], xs[it][1], xs[it][2], j[it], w);   // dead particles hold x = 0: unused
   }
   const bool boxed = stage_box<IT>(box_s, f, live, j, rel, pit);   // its barriers also publish lnh_s
-  if (!boxed && threadIdx.x == 0) atomicAdd(&a.counters[cBoxFallback], 1ull);
+  if (!boxed && threadIdx.x == 0) atomicAdd(&counter_slot(a.counters)[cBoxFallback], 1ull);
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
     // one particle after the other, its momentum and optical depth loaded
@@ -811,14 +866,13 @@ __global__ __launch_bounds__(kEIThreads) void k_emit_index(const uint64_t *mask,
   __shared__ uint32_t scan_s[16];
   __shared__ uint32_t tile_s;
   __shared__ uint64_t off_s;
-  const int64_t n = *count;
+  const int64_t n = *count, ntiles = (n + ei_tile<W>() - 1) / ei_tile<W>();
+  if (n <= 0 && blockIdx.x == 0 && threadIdx.x == 0) *n_emit = 0;
+  if (idle_block(ntiles)) return;
   while (true) {
     const uint32_t tile = next_tile(sc.ticket, &tile_s);
     const int64_t base = (int64_t)tile * ei_tile<W>();
-    if (base >= n) {
-      if (tile == 0 && threadIdx.x == 0) *n_emit = 0;
-      return;
-    }
+    if (base >= n) return;
     const int64_t w0 = (base >> 6) + (int64_t)threadIdx.x * W;
     uint64_t m[W];
     uint32_t c = 0;
@@ -848,6 +902,7 @@ __global__ __launch_bounds__(kEIThreads) void k_emit_index(const uint64_t *mask,
     }
     const int64_t last = (n - 1) / ei_tile<W>();
     if ((int64_t)tile == last && threadIdx.x == 0) *n_emit = (int64_t)(toff + total);
+    if (single_turn(ntiles)) return;
   }
 }
 
@@ -881,95 +936,196 @@ struct EmitArgs {
 // float64 and method I kernels, which need more than 128 registers.
 template <typename R, bool M1> constexpr int emit_threads() { return (sizeof(R) == 4 && !M1) ? 1024 : 512; }
 
+// What the events of one emitter leave: its photons and the event counts.
+template <typename R>
+struct EmitOut {
+  R gph[kKmaxMax];
+  double tph[kKmaxMax];
+  R nx, ny, nz, x, y, z;
+  uint32_t nacc, nev, nrej, ncap;
+};
+
+// Events of the emitter of particle i with its record; writes the lepton back.
+template <typename R, bool M1, typename Tab>
+__device__ __forceinline__ void emit_events(const EmitArgs<R> &a, const Tab &tab, const R *lnh, int64_t i,
+                                            const EmRec<R> &rc, EmitOut<R> &o) {
+  R F[6];
+#pragma unroll
+  for (int c = 0; c < 6; ++c) F[c] = rc.F[c];
+  const uint64_t id = a.lep.id[i];
+  double chi = rc.chi, W = rc.W, rem = a.dtd - rc.tau / rc.W;   // time left after the first event
+  R *PX = (R *)a.lep.px, *PY = (R *)a.lep.py, *PZ = (R *)a.lep.pz;
+  R px = rc.p[0], py = rc.p[1], pz = rc.p[2];
+  o.x = rc.x[0]; o.y = rc.x[1]; o.z = rc.x[2];
+  const R pa = sqrt(px * px + py * py + pz * pz);
+  if (pa > (R)0) { o.nx = px / pa; o.ny = py / pa; o.nz = pz / pa; }
+  R g = sqrt((R)1 + px * px + py * py + pz * pz);
+  double tau = 0.0;
+  bool recoiled = false;
+  const uint64_t step = step_of(a.step, a.d_step);
+  // one event: sample xi, infrared cut, photon, recoil (counter k of the stream)
+  auto event = [&](uint32_t k) {
+    const uint4 u = stream4(id, a.seed, step, kLeptonEvent, k);
+    R xi, om;
+    sample_rad<R>(tab, (R)chi, unit<R>(u.x), unit<R>(u.z), xi, om, a.rg);
+    const R gp = xi * g;
+    ++o.nev;
+    if (gp >= (R)2) {
+      const double tp = draw_tau(u.w);
+#pragma unroll
+      for (int s = 0; s < kKmaxMax; ++s)
+        if (s == (int)o.nacc) { o.gph[s] = gp; o.tph[s] = tp; }
+      ++o.nacc;
+      if (a.recoil) {
+        const R gn = fmax(om * g, (R)1);
+        const R pm = sqrt(fmax(gn * gn - (R)1, (R)0));
+        px = o.nx * pm; py = o.ny * pm; pz = o.nz * pm;
+        g = gn;
+        recoiled = true;
+        chi = chi_lepton(px, py, pz, F[0], F[1], F[2], F[3], F[4], F[5]);
+        W = isfinite(chi) ? kRateUnit * (double)(h_rad<R>((R)chi, lnh, a.rg) / g) : 0.0;
+      }
+    } else {
+      ++o.nrej;
+    }
+    return u;
+  };
+  if (M1 && a.gen) {
+    // method I: at most one event per sub-step, W Dt / N > r_1
+    const int N = rc.nsub;
+    int j = rc.j0, done = 0;
+    while (true) {
+      event((uint32_t)j);
+      ++done;
+      ++j;
+      if (done >= a.kmax) { if (j < N) ++o.ncap; break; }
+      if (!(W > 0.0)) break;
+      j = method1_next(id, a.seed, step, j, N, W, a.dtd);
+      if (j >= N) break;
+    }
+  } else {
+    int k = 0;
+    while (true) {
+      const uint4 u = event((uint32_t)k);
+      tau = draw_tau(u.y);
+      ++k;
+      const bool again = W > 0.0 && tau <= W * rem;
+      if (!again) break;
+      if (k >= a.kmax) { ++o.ncap; break; }
+      rem -= tau / W;
+    }
+  }
+  if (!(M1 && a.gen)) a.lep.tau[i] = tau - W * rem;
+  if (recoiled) { PX[i] = px; PY[i] = py; PZ[i] = pz; }
+}
+
 template <typename R, bool M1, typename Tab>
 __device__ void emit_tile(const EmitArgs<R> &a, const Tab &tab, const R *lnh, uint32_t tile,
                           uint64_t *scan_s, uint64_t *off_s, int64_t n_em, int64_t ph_count0,
                           uint64_t id0, uint32_t *cnt) {
   constexpr int T = emit_threads<R, M1>();
   const int64_t r = (int64_t)tile * T + threadIdx.x;
-  const bool valid = r < n_em;
-  R gph[kKmaxMax];
-  double tph[kKmaxMax];
-  uint32_t nacc = 0, nev = 0, nrej = 0, ncap = 0;
-  R nx = 0, ny = 0, nz = 0, x = 0, y = 0, z = 0;
-  if (valid) {
+  EmitOut<R> o;
+  o.nacc = o.nev = o.nrej = o.ncap = 0;
+  o.nx = o.ny = o.nz = o.x = o.y = o.z = 0;
+  if (r < n_em) {
     const EmIdx e = a.em_idx[r];
-    const int64_t i = e.i;
     const EmRec<R> rc = a.rec[e.slot];
-    R F[6];
-#pragma unroll
-    for (int c = 0; c < 6; ++c) F[c] = rc.F[c];
-    const uint64_t id = a.lep.id[i];
-    double chi = rc.chi, W = rc.W, rem = a.dtd - rc.tau / rc.W;   // time left after the first event
-    R *PX = (R *)a.lep.px, *PY = (R *)a.lep.py, *PZ = (R *)a.lep.pz;
-    R px = rc.p[0], py = rc.p[1], pz = rc.p[2];
-    x = rc.x[0]; y = rc.x[1]; z = rc.x[2];
-    const R pa = sqrt(px * px + py * py + pz * pz);
-    if (pa > (R)0) { nx = px / pa; ny = py / pa; nz = pz / pa; }
-    R g = sqrt((R)1 + px * px + py * py + pz * pz);
-    double tau = 0.0;
-    bool recoiled = false;
-    const uint64_t step = step_of(a.step, a.d_step);
-    // one event: sample xi, infrared cut, photon, recoil (counter k of the stream)
-    auto event = [&](uint32_t k) {
-      const uint4 u = stream4(id, a.seed, step, kLeptonEvent, k);
-      R xi, om;
-      sample_rad<R>(tab, (R)chi, unit<R>(u.x), unit<R>(u.z), xi, om, a.rg);
-      const R gp = xi * g;
-      ++nev;
-      if (gp >= (R)2) {
-#pragma unroll
-        for (int s = 0; s < kKmaxMax; ++s)
-          if (s == (int)nacc) { gph[s] = gp; tph[s] = -log(unit<double>(u.w)); }
-        ++nacc;
-        if (a.recoil) {
-          const R gn = fmax(om * g, (R)1);
-          const R pm = sqrt(fmax(gn * gn - (R)1, (R)0));
-          px = nx * pm; py = ny * pm; pz = nz * pm;
-          g = gn;
-          recoiled = true;
-          chi = chi_lepton(px, py, pz, F[0], F[1], F[2], F[3], F[4], F[5]);
-          W = isfinite(chi) ? kRateUnit * (double)(h_rad<R>((R)chi, lnh, a.rg) / g) : 0.0;
-        }
-      } else {
-        ++nrej;
-      }
-      return u;
-    };
-    if (M1 && a.gen) {
-      // method I: at most one event per sub-step, W Dt / N > r_1
-      const int N = rc.nsub;
-      int j = rc.j0, done = 0;
-      while (true) {
-        event((uint32_t)j);
-        ++done;
-        ++j;
-        if (done >= a.kmax) { if (j < N) ++ncap; break; }
-        if (!(W > 0.0)) break;
-        j = method1_next(id, a.seed, step, j, N, W, a.dtd);
-        if (j >= N) break;
-      }
-    } else {
-      int k = 0;
-      while (true) {
-        const uint4 u = event((uint32_t)k);
-        tau = -log(unit<double>(u.y));
-        ++k;
-        const bool again = W > 0.0 && tau <= W * rem;
-        if (!again) break;
-        if (k >= a.kmax) { ++ncap; break; }
-        rem -= tau / W;
-      }
-    }
-    if (!(M1 && a.gen)) a.lep.tau[i] = tau - W * rem;
-    if (recoiled) { PX[i] = px; PY[i] = py; PZ[i] = pz; }
+    emit_events<R, M1>(a, tab, lnh, e.i, rc, o);
   }
-  count_lds(cnt, cEvents, nev);
-  count_lds(cnt, cRejected, nrej);
-  count_lds(cnt, cCapped, ncap);
-  count_lds(cnt, cPhotons, nacc);
-  append_photons<R>(a.ph, a.ret, step_of(a.step, a.d_step), a.dtd, tile, n_em, T, nacc, gph, tph, x, y, z, nx, ny,
-                    nz, ph_count0, id0, a.next_id, a.sc, a.counters, scan_s, off_s, cnt);
+  count_lds(cnt, cEvents, o.nev);
+  count_lds(cnt, cRejected, o.nrej);
+  count_lds(cnt, cCapped, o.ncap);
+  count_lds(cnt, cPhotons, o.nacc);
+  append_photons<R>(a.ph, a.ret, step_of(a.step, a.d_step), a.dtd, tile, n_em, T, o.nacc, o.gph, o.tph, o.x, o.y, o.z,
+                    o.nx, o.ny, o.nz, ph_count0, id0, a.next_id, a.sc, a.counters, scan_s, off_s, cnt);
+}
+
+// Small species (the launcher takes them for capacities up to kEmitSmall, 2^17: at
+// 1e5 electrons a step is 7 to 10 us shorter than with a list, at 3e5, where 1172
+// tickets follow each other, 8 to 20 us longer): index
+// and emission in one launch.  A workgroup takes 256 consecutive particles from the
+// ticket and packs the emitters of their four mask words into its first lanes, so
+// that no list is built and a wave without an emitter only waits.  The kernel's
+// time is its chain of loads (ticket, mask, record, table) and the instructions of
+// an event, one event after the other for the emitters with several; the launches
+// saved are most of the call.  Push and emission of 24000 float32 electrons take
+// 19 us a step (33 with a list and two clearing launches), of 1e5 float64 ones 27
+// (37).
+constexpr int kESTile = 256, kESWords = kESTile / 64;
+
+template <typename R> struct EmitTab;
+template <> struct EmitTab<float> {
+  static __device__ __forceinline__ RowQ16 get(const EmitArgs<float> &a) { return RowQ16{a.q16, a.s0sc}; }
+};
+template <> struct EmitTab<double> {
+  static __device__ __forceinline__ RowF64 get(const EmitArgs<double> &a) { return RowF64{a.S64}; }
+};
+
+// Emitter r of a tile with mask words m: its word, its rank there (which places its
+// record) and the position of that set bit; false if the tile has fewer.
+__device__ __forceinline__ bool tile_emitter(const uint64_t m[kESWords], int r, int &w, int &rank, int &bit) {
+  w = 0;
+  rank = r;
+  uint64_t mw = m[0];
+#pragma unroll
+  for (int k = 0; k < kESWords - 1; ++k) {
+    const int c = __popcll(m[k]);
+    if (w == k && rank >= c) { rank -= c; ++w; mw = m[k + 1]; }
+  }
+  if (rank >= __popcll(mw)) return false;
+  int left = rank;
+  bit = 0;
+#pragma unroll
+  for (int h = 32; h > 0; h >>= 1) {
+    const int c = __popcll((mw >> bit) & ((1ull << h) - 1ull));
+    if (left >= c) { left -= c; bit += h; }
+  }
+  return true;
+}
+
+template <typename R, bool M1>
+__global__ __launch_bounds__(kESTile) void k_emit_small(EmitArgs<R> a, const uint64_t *mask) {
+  __shared__ R lnh_s[kRadNChi];
+  __shared__ uint64_t scan_s[16], off_s;
+  __shared__ uint32_t tile_s, cnt_s[cNumCounters];
+  __shared__ int64_t hdr_s[2];
+  const int64_t n = *a.lep.count, ntiles = (n + kESTile - 1) / kESTile;
+  if (idle_block(ntiles)) return;
+  count_zero(cnt_s);
+  if (threadIdx.x == 0) { hdr_s[0] = *a.ph.count; hdr_s[1] = (int64_t)*a.next_id; }
+  static_assert(kRadNChi == kESTile, "a thread stages one rate");
+  lnh_s[threadIdx.x] = a.lnh[threadIdx.x];
+  const auto tab = EmitTab<R>::get(a);
+  while (true) {
+    const uint32_t tile = next_tile(a.sc.ticket, &tile_s);   // its barriers also publish the header and ln h
+    if ((int64_t)tile >= ntiles) break;
+    const int64_t base = (int64_t)tile * kESTile;
+    uint64_t m[kESWords];
+#pragma unroll
+    for (int k = 0; k < kESWords; ++k) {
+      const int64_t valid = n - base - 64 * k;
+      m[k] = valid > 0 ? mask[(base >> 6) + k] : 0;
+      if (valid > 0 && valid < 64) m[k] &= (1ull << valid) - 1ull;
+    }
+    EmitOut<R> o;
+    o.nacc = o.nev = o.nrej = o.ncap = 0;
+    o.nx = o.ny = o.nz = o.x = o.y = o.z = 0;
+    int w, rank, bit;
+    if (tile_emitter(m, threadIdx.x, w, rank, bit)) {
+      const EmRec<R> rc = a.rec[base + 64 * w + rank];   // (rec_slot)
+      emit_events<R, M1>(a, tab, lnh_s, base + 64 * w + bit, rc, o);
+    }
+    count_lds(cnt_s, cEvents, o.nev);
+    count_lds(cnt_s, cRejected, o.nrej);
+    count_lds(cnt_s, cCapped, o.ncap);
+    count_lds(cnt_s, cPhotons, o.nacc);
+    append_photons<R>(a.ph, a.ret, step_of(a.step, a.d_step), a.dtd, tile, n, kESTile, o.nacc, o.gph, o.tph, o.x, o.y,
+                      o.z, o.nx, o.ny, o.nz, hdr_s[0], (uint64_t)hdr_s[1], a.next_id, a.sc, a.counters, scan_s,
+                      &off_s, cnt_s);
+    if (single_turn(ntiles)) break;
+  }
+  count_flush(cnt_s, a.counters);
 }
 
 // float path: 16-bit quantile table read through the caches (an emission step
@@ -987,13 +1143,15 @@ __global__ __launch_bounds__((emit_threads<float, M1>())) void k_emit_f32(EmitAr
   __syncthreads();
   const int64_t n_em = hdr_s[0], ph0 = hdr_s[1];
   const uint64_t id0 = (uint64_t)hdr_s[2];
-  if (n_em == 0) return;
+  const int64_t ntiles = (n_em + emit_threads<float, M1>() - 1) / emit_threads<float, M1>();
+  if (idle_block(ntiles)) return;
   for (int k = threadIdx.x; k < kRadNChi; k += blockDim.x) lnh_s[k] = a.lnh[k];
   const RowQ16 tab{a.q16, a.s0sc};     // 16-bit quantile table through the caches
   while (true) {
     const uint32_t tile = next_tile(a.sc.ticket, &tile_s);
-    if ((int64_t)tile * emit_threads<float, M1>() >= n_em) break;
+    if ((int64_t)tile >= ntiles) break;
     emit_tile<float, M1>(a, tab, lnh_s, tile, scan_s, &off_s, n_em, ph0, id0, cnt_s);
+    if (single_turn(ntiles)) break;
   }
   count_flush(cnt_s, a.counters);
 }
@@ -1012,13 +1170,15 @@ __global__ __launch_bounds__((emit_threads<double, M1>())) void k_emit_f64(EmitA
   __syncthreads();
   const int64_t n_em = hdr_s[0], ph0 = hdr_s[1];
   const uint64_t id0 = (uint64_t)hdr_s[2];
-  if (n_em == 0) return;
+  const int64_t ntiles = (n_em + emit_threads<double, M1>() - 1) / emit_threads<double, M1>();
+  if (idle_block(ntiles)) return;
   for (int k = threadIdx.x; k < kRadNChi; k += blockDim.x) lnh_s[k] = a.lnh[k];
   const RowF64 tab{a.S64};
   while (true) {
     const uint32_t tile = next_tile(a.sc.ticket, &tile_s);
-    if ((int64_t)tile * emit_threads<double, M1>() >= n_em) break;
+    if ((int64_t)tile >= ntiles) break;
     emit_tile<double, M1>(a, tab, lnh_s, tile, scan_s, &off_s, n_em, ph0, id0, cnt_s);
+    if (single_turn(ntiles)) break;
   }
   count_flush(cnt_s, a.counters);
 }
@@ -1124,7 +1284,8 @@ struct EmitMlpLds {
 // order.
 template <bool Cont>
 __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a, MlpDev m, uint64_t *cont_mask,
-                                                              const int32_t *cont_idx, const int64_t *n_cont) {
+                                                              const int32_t *cont_idx, const int64_t *n_cont,
+                                                              ScanClear clear) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   EmitMlpLds &S = *reinterpret_cast<EmitMlpLds *>(lds_raw);
   __shared__ uint64_t scan_s[16];
@@ -1132,6 +1293,7 @@ __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a,
   __shared__ uint64_t off_s;
   __shared__ int64_t hdr_s[3];
   __shared__ uint32_t cnt_s[cNumCounters];
+  if (!Cont) scan_clear(clear);
   count_zero(cnt_s);
   if (threadIdx.x == 0) {
     hdr_s[0] = Cont ? *n_cont : *a.n_emit;
@@ -1141,7 +1303,8 @@ __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a,
   __syncthreads();
   const int64_t n_em = hdr_s[0], ph0 = hdr_s[1];
   const uint64_t id0 = (uint64_t)hdr_s[2];
-  if (n_em == 0) return;
+  const int64_t ntiles = (n_em + kEmitMlpThreads - 1) / kEmitMlpThreads;
+  if (idle_block(ntiles)) return;
   const int klim = Cont ? a.kmax : 1;
   mlp::stage_net_infer(m.thA, mlp::kA, &S.A);
   mlp::stage_net_infer(m.thB, mlp::kB, &S.B);
@@ -1151,7 +1314,7 @@ __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a,
   const uint64_t step = step_of(a.step, a.d_step);
   while (true) {
     const uint32_t tile = next_tile(a.sc.ticket, &tile_s);
-    if ((int64_t)tile * kEmitMlpThreads >= n_em) break;
+    if ((int64_t)tile >= ntiles) break;
     const int64_t r = (int64_t)tile * kEmitMlpThreads + threadIdx.x;
     const bool valid = r < n_em;
     float gph[kKmaxMax];
@@ -1237,9 +1400,10 @@ __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a,
         const float gp = xi * g;
         if (gp >= 2.f) {
           if (counted) {
+            const double tp = draw_tau(u.w);
 #pragma unroll
             for (int sl = 0; sl < kKmaxMax; ++sl)
-              if (sl == (int)nacc) { gph[sl] = gp; tph[sl] = -log(unit<double>(u.w)); }
+              if (sl == (int)nacc) { gph[sl] = gp; tph[sl] = tp; }
             ++nacc;
           }
           if (a.recoil) {
@@ -1257,7 +1421,7 @@ __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a,
         }
       }
       if (active) {
-        tau = -log(unit<double>(u.y));
+        tau = draw_tau(u.y);
         const bool again = Wenv > 0.0 && tau <= Wenv * rem;
         if (!again) {
           active = false;
@@ -1290,6 +1454,7 @@ __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a,
     count_lds(cnt_s, cEnvelopeExceeded, nexc);
     append_photons<float>(a.ph, a.ret, step, a.dtd, tile, n_em, kEmitMlpThreads, nacc, gph, tph, x, y, z, nx, ny, nz,
                           ph0, id0, a.next_id, a.sc, a.counters, scan_s, &off_s, cnt_s);
+    if (single_turn(ntiles)) break;
   }
   count_flush(cnt_s, a.counters);
 }
@@ -1317,7 +1482,7 @@ struct PairArgs {
   RetireDev ret;
 };
 
-constexpr int kPairThreads = 256, kPairItems = 4, kPairTile = kPairThreads * kPairItems;
+constexpr int kPairThreads = 256;
 
 // Field, chi_ph and pair rate of photon i after its move; false if the fields
 // are not finite (then chi is NaN and W = 0).
@@ -1344,16 +1509,23 @@ __device__ __forceinline__ bool photon_rate(const PairArgs<R> &a, const R *L, in
   return photon_rate_at<R>(a, L, F, kx, ky, kz, gph, chi, W);
 }
 
-// Float64 pair pass.  One tile of kPairTile photons, kPairItems per thread (photon base + it *
+// Float64 pair pass.  One tile of Items photons per thread (photon base + it *
 // kPairThreads + thread, so that a pass over `it` is coalesced).  Pass 1 moves
 // every photon and decides its event; the offsets of the pairs follow the photon
 // index through one scan of per-level counts packed 16 bits per level; pass 2
-// recomputes the (rare) events from the photon's stream and writes the pairs.
-template <typename R, typename Tab>
+// makes the (rare) events' pairs from the photon's stream (with several photons per
+// thread it evaluates chi again).  Four photons per thread where there are enough
+// of them to fill the GPU; one in a small species (kPairSmall), whose time is the
+// latency of a tile: a call takes 14 us with 2e4 photons (31 with four per thread),
+// 20 with 1e5 (34), 35 with 2.6e5 (35), 59 with four per thread and 1e6.
+constexpr int64_t kPairSmall = (int64_t)1 << 18;
+
+template <int kPairItems, typename R, typename Tab>
 __device__ void pair_tile(const PairArgs<R> &a, const Tab &tab, const R *L, uint32_t tile,
                           uint64_t *scan_s, uint64_t *off_s, int64_t n, int64_t e0, int64_t p0,
                           uint64_t id0, uint32_t *cnt) {
   static_assert(kPairThreads <= 0xFFFF, "per-level counts are packed in 16 bits");
+  constexpr int kPairTile = kPairThreads * kPairItems;
   const int64_t base = (int64_t)tile * kPairTile;
   R *X = (R *)a.ph.x, *Y = (R *)a.ph.y, *Z = (R *)a.ph.z;
   const R *KX = (const R *)a.ph.px, *KY = (const R *)a.ph.py, *KZ = (const R *)a.ph.pz;
@@ -1365,7 +1537,7 @@ __device__ void pair_tile(const PairArgs<R> &a, const Tab &tab, const R *L, uint
   const bool need_x = a.move || a.f.kind == QED_FIELD_GRID;
   uint64_t pids[kPairItems];
   R kk[kPairItems][3], xx[kPairItems][3];
-  double taus[kPairItems];
+  double taus[kPairItems], chi1 = 0.0;
 #pragma unroll
   for (int it = 0; it < kPairItems; ++it) {
     const int64_t i = base + (int64_t)it * kPairThreads + threadIdx.x;
@@ -1402,6 +1574,7 @@ __device__ void pair_tile(const PairArgs<R> &a, const Tab &tab, const R *L, uint
     } else {
       ++nnan;
     }
+    chi1 = chi;
     const double tau = taus[it];
     if (W > 0.0 && tau <= W * a.dtd) {
       evbits |= 1u << it;
@@ -1440,15 +1613,15 @@ __device__ void pair_tile(const PairArgs<R> &a, const Tab &tab, const R *L, uint
     const R kx = KX[i], ky = KY[i], kz = KZ[i];
     const R x = X[i], y = Y[i], z = Z[i];
     const R gph = root<R>(kx * kx + ky * ky + kz * kz);
-    double chi, W;
-    photon_rate<R>(a, L, i, x, y, z, kx, ky, kz, gph, chi, W);
+    double chi = chi1, W;
+    if constexpr (kPairItems > 1) photon_rate<R>(a, L, i, x, y, z, kx, ky, kz, gph, chi, W);
     const uint4 u = stream4(pid, a.seed, step_of(a.step, a.d_step), kPhotonEvent, 0u);
     R xh, omh;
     sample_pair_half<R>(tab, (R)chi, unit<R>(u.x), unit<R>(u.y), xh, omh, a.rg);
     const bool flip = u.y & 1u;
     const R xe = flip ? omh : xh, xp = flip ? xh : omh;
     const R ge = xe * gph, gpos = xp * gph;
-    const double te = -log(unit<double>(u.z)), tp = -log(unit<double>(u.w));
+    const double te = draw_tau(u.z), tp = draw_tau(u.w);
     a.ph.id[i] = kDeadId;
     const uint64_t rank = toff + level0[it] + (uint32_t)((excl >> (16 * it)) & 0xFFFFu);
     const int64_t je = e0 + (int64_t)rank, jp = p0 + (int64_t)rank;
@@ -1516,8 +1689,9 @@ __device__ __forceinline__ double photon_envelope(const PairArgs<float> &a, doub
 
 // FieldFree: the envelope of the retirement's field bound (no field gathered).
 template <bool FieldFree>
-__global__ __launch_bounds__(kPTThreads) void k_photon_thin(PairArgs<float> a, uint64_t *cmask) {
+__global__ __launch_bounds__(kPTThreads) void k_photon_thin(PairArgs<float> a, uint64_t *cmask, ScanClear clear) {
   __shared__ uint32_t cnt_s[cNumCounters];
+  scan_clear(clear);
   count_zero(cnt_s);
   __syncthreads();
   const int64_t n = *a.ph.count;
@@ -1612,7 +1786,8 @@ __global__ __launch_bounds__(kPCThreads) void k_pair_cand(PairArgs<float> a, con
   __syncthreads();
   const int64_t nc = hdr_s[0], e0 = hdr_s[1], p0 = hdr_s[2];
   const uint64_t id0 = (uint64_t)hdr_s[3];
-  if (nc == 0) return;
+  const int64_t ntiles = (nc + kPCThreads - 1) / kPCThreads;
+  if (idle_block(ntiles)) return;
   mlp::stage_net_infer(thB, mlp::kB, &B_s);
   for (int k = threadIdx.x; k < kPairNRate; k += blockDim.x) L_s[k] = a.L[k];
   const RowQ16 tab{a.q16, a.s0sc};
@@ -1623,7 +1798,7 @@ __global__ __launch_bounds__(kPCThreads) void k_pair_cand(PairArgs<float> a, con
   uint32_t nrange = 0, nnan = 0, nev = 0, nnull = 0, nfr = 0, ncap = 0, nexc = 0, nret = 0, ndrop = 0;
   while (true) {
     const uint32_t tile = next_tile(a.sc.ticket, &tile_s);   // its barriers also publish the staged net
-    if ((int64_t)tile * kPCThreads >= nc) break;
+    if ((int64_t)tile >= ntiles) break;
     const int64_t r = (int64_t)tile * kPCThreads + threadIdx.x;
     const bool valid = r < nc;
     const int64_t i = valid ? (int64_t)cidx[r] : 0;
@@ -1673,7 +1848,7 @@ __global__ __launch_bounds__(kPCThreads) void k_pair_cand(PairArgs<float> a, con
           const uint4 u = k == 0 ? u0 : stream4(pid, a.seed, step, kPhotonThin, (uint32_t)k);
           if (unit<double>(u.x) * We < W) { ev = true; break; }
           ++nnull;
-          tau = -log(unit<double>(u.y));
+          tau = draw_tau(u.y);
           if (!(tau <= We * rem)) { photon_settle(a, i, tau - We * rem, gph, t_left, nret); break; }
           if (k + 1 >= kmax) { ++ncap; photon_settle(a, i, tau - We * rem, gph, t_left, nret); break; }
           rem -= tau / We;
@@ -1691,7 +1866,7 @@ __global__ __launch_bounds__(kPCThreads) void k_pair_cand(PairArgs<float> a, con
       const bool flip = u.y & 1u;
       const float xe = flip ? omh : xh, xp = flip ? xh : omh;
       const float ge = xe * gph, gpos = xp * gph;
-      const double te = -log(unit<double>(u.z)), tp = -log(unit<double>(u.w));
+      const double te = draw_tau(u.z), tp = draw_tau(u.w);
       a.ph.id[i] = kDeadId;
       const uint64_t rank = toff + excl;
       const int64_t je = e0 + (int64_t)rank, jp = p0 + (int64_t)rank;
@@ -1715,6 +1890,7 @@ __global__ __launch_bounds__(kPCThreads) void k_pair_cand(PairArgs<float> a, con
       *a.next_id = id0 + 2 * (uint64_t)tt;
       if (a.killed) atomicAdd((unsigned long long *)a.killed, (unsigned long long)tt);
     }
+    if (single_turn(ntiles)) break;
   }
   count_lds(cnt_s, cChiRange, nrange);
   count_lds(cnt_s, cNanChi, nnan);
@@ -1744,9 +1920,11 @@ __global__ __launch_bounds__(kPCThreads) void k_pair_cand(PairArgs<float> a, con
 // 168 on a grid (three waves: its four 27-node gathers in flight).
 template <int FK> constexpr int pt_waves() { return FK == QED_FIELD_GRID ? 3 : 4; }
 template <int FK>
-__global__ __launch_bounds__(kPTThreads, (pt_waves<FK>())) void k_photon_table(PairArgs<float> a, uint64_t *emask) {
+__global__ __launch_bounds__(kPTThreads, (pt_waves<FK>())) void k_photon_table(PairArgs<float> a, uint64_t *emask,
+                                                                                   ScanClear clear) {
   __shared__ float L_s[kPairNRate];
   __shared__ uint32_t cnt_s[cNumCounters];
+  scan_clear(clear);
   count_zero(cnt_s);
   for (int k = threadIdx.x; k < kPairNRate; k += blockDim.x) L_s[k] = a.L[k];
   __syncthreads();
@@ -1855,7 +2033,7 @@ __global__ __launch_bounds__(256) void k_pair_events(PairArgs<float> a, const in
     const bool flip = u.y & 1u;
     const float xe = flip ? omh : xh, xp = flip ? xh : omh;
     const float ge = xe * gph, gpos = xp * gph;
-    const double te = -log(unit<double>(u.z)), tp = -log(unit<double>(u.w));
+    const double te = draw_tau(u.z), tp = draw_tau(u.w);
     a.ph.id[i] = kDeadId;
     const int64_t je = e0 + r, jp = p0 + r;
     if (je < a.el.cap && jp < a.po.cap) {
@@ -1885,7 +2063,9 @@ __global__ void k_pair_commit(PairArgs<float> a, const int64_t *n_ev) {
   if (a.killed && tt) atomicAdd((unsigned long long *)a.killed, (unsigned long long)tt);
 }
 
+template <int Items>
 __global__ __launch_bounds__(kPairThreads) void k_pairs_f64(PairArgs<double> a) {
+  constexpr int kPairTile = kPairThreads * Items;
   __shared__ double L_s[kPairNRate];
   __shared__ uint64_t scan_s[16];
   __shared__ uint32_t tile_s;
@@ -1900,13 +2080,14 @@ __global__ __launch_bounds__(kPairThreads) void k_pairs_f64(PairArgs<double> a) 
   __syncthreads();
   const int64_t n = hdr_s[0], e0 = hdr_s[1], p0 = hdr_s[2];
   const uint64_t id0 = (uint64_t)hdr_s[3];
-  if (n == 0) return;
+  const int64_t ntiles = (n + kPairTile - 1) / kPairTile;
+  if (idle_block(ntiles)) return;
   for (int k = threadIdx.x; k < kPairNRate; k += blockDim.x) L_s[k] = a.L[k];
   const RowF64 tab{a.S64};
   while (true) {
-    const uint32_t tile = next_tile(a.sc.ticket, &tile_s);
-    if ((int64_t)tile * kPairTile >= n) break;
-    pair_tile<double>(a, tab, L_s, tile, scan_s, &off_s, n, e0, p0, id0, cnt_s);
+    const uint32_t tile = next_tile_clean(a.sc, &tile_s, ntiles);
+    if ((int64_t)tile >= ntiles) break;
+    pair_tile<Items, double>(a, tab, L_s, tile, scan_s, &off_s, n, e0, p0, id0, cnt_s);
   }
   count_flush(cnt_s, a.counters);
   // retired photons are dead too: the compaction of this species must not skip
@@ -1926,15 +2107,24 @@ __global__ __launch_bounds__(kCThreads) void k_compact(SpeciesDev sp, ScanDev sc
   // killed: particles marked dead since the last compaction of this species, when
   // known (pair creation keeps it); nothing to do if none
   if (killed && *killed == 0) return;
-  const int64_t n = *sp.count;
+  // (the count and `killed` change only once every workgroup has read them, when
+  // the last ticket of all is drawn)
+  const int64_t n = *sp.count, ntiles = (n + kCTile - 1) / kCTile;
+  if (idle_block(ntiles) && (ntiles > 0 || blockIdx.x > 0)) return;
   R *A[6] = {(R *)sp.x, (R *)sp.y, (R *)sp.z, (R *)sp.px, (R *)sp.py, (R *)sp.pz};
   while (true) {
-    const uint32_t tile = next_tile(sc.ticket, &tile_s);
+    const uint32_t tile = next_tile_clean(sc, &tile_s, ntiles, [&] {
+      if (n) {
+        const int64_t nn = (int64_t)(ld_status(&sc.status[ntiles - 1]) & kValMask);
+        if (nn < n) {
+          atomicAdd(&counters[cCompacted], (unsigned long long)(n - nn));
+          *sp.count = nn;
+        }
+      }
+      if (killed) *killed = 0;
+    });
     const int64_t base = (int64_t)tile * kCTile;
-    if (base >= n) {
-      if (tile == 0 && killed && threadIdx.x == 0) *killed = 0;
-      break;
-    }
+    if (base >= n) break;
     R v[kCItems][6];
     double tau[kCItems];
     uint64_t id[kCItems];
@@ -1969,14 +2159,6 @@ __global__ __launch_bounds__(kCThreads) void k_compact(SpeciesDev sp, ScanDev sc
         ++r;
       }
     }
-    const int64_t last = (n - 1) / kCTile;
-    if ((int64_t)tile == last && threadIdx.x == 0) {
-      // every tile has been claimed: workgroups that start later find no tile
-      const int64_t nn = (int64_t)(toff + total);
-      atomicAdd(&counters[cCompacted], (unsigned long long)(n - nn));
-      *sp.count = nn;
-      if (killed) *killed = 0;
-    }
   }
 }
 
@@ -1989,14 +2171,6 @@ __global__ void k_zero_scan(uint32_t *ticket, uint64_t *status, int64_t n) {
   if (i < n) status[i] = 0;
 }
 
-// Both scan regions at once: words [0, n0) of region 0, [0, n1) of region 1.
-__global__ void k_zero_scan2(uint32_t *ticket, uint64_t *status, int64_t len, int64_t n0, int64_t n1) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i == 0) { ticket[0] = 0; ticket[1] = 0; }
-  if (i < n0) status[i] = 0;
-  if (i < n1) status[len + i] = 0;
-}
-
 __global__ void k_init_tau(const uint64_t *id, double *tau, const int64_t *count, uint32_t seed,
                            uint64_t step_v, const int64_t *d_step, int64_t cap) {
   const int64_t n = *count;
@@ -2004,7 +2178,7 @@ __global__ void k_init_tau(const uint64_t *id, double *tau, const int64_t *count
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n && i < cap;
        i += (int64_t)gridDim.x * blockDim.x) {
     const uint4 u = stream4(id[i], seed, step, kInitTau, 0u);
-    tau[i] = -log(unit<double>(u.x));
+    tau[i] = draw_tau(u.x);
   }
 }
 
@@ -2131,8 +2305,14 @@ static hipError_t zero_scan_at(uint32_t *ticket, uint64_t *status, int64_t statu
   return hipGetLastError();
 }
 
-static hipError_t zero_scan(qed_ctx *c, int64_t ntiles, hipStream_t st) {
-  return zero_scan_at(c->d_ticket, c->d_status, c->status_len, ntiles, st);   // reserve() sizes it
+static ScanDev scan_region(const qed_ctx *c, int k) { return ScanDev{c->d_ticket + k, c->d_status + c->region_at[k]}; }
+
+// Adds region k with n status words to those a kernel clears.
+static hipError_t clear_region(const qed_ctx *c, ScanClear &cl, int at, int k, int64_t n) {
+  if (n > c->region_len[k]) return hipErrorInvalidValue;   // the context's reservation sizes the regions
+  cl.r[at] = scan_region(c, k);
+  cl.n[at] = n;
+  return hipSuccess;
 }
 
 // Blocks of a gather/push launch for a species of this capacity, IT particles
@@ -2215,93 +2395,116 @@ hipError_t launch_gather_push(qed_ctx *c, const qed_fields_t *f, const qed_speci
   const int64_t *dstep = step < 0 ? c->d_step : nullptr;
   const int64_t cap = sp->capacity;
   const bool use_mlp = (c->params.flags & QED_FLAG_SURROGATE) && sp->dtype == QED_F32;
+  // the scan regions of the emission that follows (index tiles of at least 16384
+  // particles, emission tiles of at least 512 emitters, of 256 particles in a small
+  // species)
+  ScanClear clear{};
+  hipError_t e = clear_region(c, clear, 0, kRegEmitIndex, cap / ei_tile<1>() + 1);
+  if (e == hipSuccess) e = clear_region(c, clear, 1, kRegEmit, cap / (cap <= kEmitSmall ? kESTile : 512) + 1);
+  if (e == hipSuccess && use_mlp) e = clear_region(c, clear, 2, kRegEmitCont, cap / 512 + 1);
+  if (e != hipSuccess) return e;
   if (use_mlp) {
     // surrogate path: the same pass with the rate envelope (thinning); the
     // emission pass evaluates the nets at the candidates
     GPArgs<float> a{dev_species(sp), dev_fields(f), c->rad_lnh32, (float)charge, (float)dt, dt, c->em_mask,
-                    (EmRec<float> *)c->em_rec, c->d_counters, 0, c->params.seed, (uint64_t)step, dstep, c->range};
+                    (EmRec<float> *)c->em_rec, c->d_counters, 0, c->params.seed, (uint64_t)step, dstep, c->range, clear};
     launch_gp_kind_m<float, false, true>(a, f->kind, cap, gp_dense(f, sp), st);
   } else if (sp->dtype == QED_F32) {
     GPArgs<float> a{dev_species(sp), dev_fields(f), c->rad_lnh32, (float)charge, (float)dt, dt, c->em_mask,
-                    (EmRec<float> *)c->em_rec, c->d_counters, gen, c->params.seed, (uint64_t)step, dstep, c->range};
+                    (EmRec<float> *)c->em_rec, c->d_counters, gen, c->params.seed, (uint64_t)step, dstep, c->range, clear};
     launch_gp_kind<float>(a, f->kind, cap, gp_dense(f, sp), st);
   } else {
     GPArgs<double> a{dev_species(sp), dev_fields(f), c->rad_lnh64, (double)charge, dt, dt, c->em_mask,
-                     (EmRec<double> *)c->em_rec, c->d_counters, gen, c->params.seed, (uint64_t)step, dstep, c->range};
+                     (EmRec<double> *)c->em_rec, c->d_counters, gen, c->params.seed, (uint64_t)step, dstep, c->range, clear};
     launch_gp_kind<double>(a, f->kind, cap, false, st);
   }
   return hipGetLastError();
 }
 
+template <typename R> static const R *rad_lnh(const qed_ctx *c);
+template <> const float *rad_lnh<float>(const qed_ctx *c) { return c->rad_lnh32; }
+template <> const double *rad_lnh<double>(const qed_ctx *c) { return c->rad_lnh64; }
+
+template <typename R>
+static EmitArgs<R> emit_args(qed_ctx *c, const qed_species_t *lep, const qed_species_t *ph, int64_t step, int recoil,
+                             const ScanDev &sc) {
+  return EmitArgs<R>{dev_species(lep), dev_species(ph), rad_lnh<R>(c), c->rad_S64, c->rad_q16, c->rad_s0sc,
+                     c->em_idx, (const EmRec<R> *)c->em_rec, c->d_n_emit, c->d_next_id, c->params.seed,
+                     c->params.kmax, recoil, (uint64_t)step, step < 0 ? c->d_step : nullptr, sc, c->d_counters,
+                     gen_mode(c), c->em_dt, c->range, retire_dev(c)};
+}
+
+template <typename R>
+static void launch_emit_small(qed_ctx *c, const EmitArgs<R> &a, int64_t cap, bool m1, hipStream_t st) {
+  const dim3 grid((unsigned)((cap + kESTile - 1) / kESTile));   // a workgroup for each tile
+  if (m1) hipLaunchKernelGGL((k_emit_small<R, true>), grid, dim3(kESTile), 0, st, a, c->em_mask);
+  else hipLaunchKernelGGL((k_emit_small<R, false>), grid, dim3(kESTile), 0, st, a, c->em_mask);
+}
+
 hipError_t launch_emit(qed_ctx *c, const qed_species_t *lep, const qed_species_t *ph, int64_t step,
                        hipStream_t st) {
   const bool use_mlp = lep->dtype == QED_F32 && (c->params.flags & QED_FLAG_SURROGATE);
+  const bool m1 = gen_mode(c) != 0;
+  const ScanDev isc = scan_region(c, kRegEmitIndex), sc = scan_region(c, kRegEmit);   // cleared by k_gather_push
+  const int64_t *dstep = step < 0 ? c->d_step : nullptr;
+  const int recoil = (c->params.flags & QED_FLAG_NO_RECOIL) ? 0 : 1;
+  // up to kEmitSmall particles the tables' emission takes its emitters from the
+  // mask words themselves; above, a list gives every lane an emitter
+  if (!use_mlp && lep->capacity <= kEmitSmall) {
+    if (lep->dtype == QED_F32)
+      launch_emit_small(c, emit_args<float>(c, lep, ph, step, recoil, sc), lep->capacity, m1, st);
+    else
+      launch_emit_small(c, emit_args<double>(c, lep, ph, step, recoil, sc), lep->capacity, m1, st);
+    return hipGetLastError();
+  }
   // ordered emitter list from the mask of the last gather/push
   const bool wide = lep->capacity >= kEIWideFrom;
   const int64_t eit = wide ? ei_tile<8>() : ei_tile<1>();
   const int64_t etiles = (lep->capacity + eit - 1) / eit;
   const unsigned eig = (unsigned)(etiles < 2 * (int64_t)c->n_cu ? etiles : 2 * (int64_t)c->n_cu);   // persistent
-  // one launch clears both scans: region 1 for the index, region 0 for the events
-  const bool m1 = gen_mode(c) != 0;
   const int tile = use_mlp ? kEmitMlpThreads
                            : (lep->dtype == QED_F32 ? (m1 ? emit_threads<float, true>() : emit_threads<float, false>())
                                                     : (m1 ? emit_threads<double, true>() : emit_threads<double, false>()));
   const int64_t ntiles = (lep->capacity + tile - 1) / tile;
-  const int64_t n0 = ntiles + 1, n1 = etiles + 1, nz = n0 > n1 ? n0 : n1;
-  if (nz > c->status_len) return hipErrorInvalidValue;   // reserve() sizes the status regions
-  hipLaunchKernelGGL(k_zero_scan2, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, c->d_ticket, c->d_status,
-                     c->status_len, n0, n1);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const ScanDev isc{c->d_ticket + 1, c->d_status + c->status_len};
+  if (ntiles > c->region_len[kRegEmit] || etiles > c->region_len[kRegEmitIndex]) return hipErrorInvalidValue;
   if (wide)
     hipLaunchKernelGGL((k_emit_index<8, EmIdx>), dim3(eig), dim3(kEIThreads), 0, st, c->em_mask, lep->count,
-                     c->em_idx, c->d_n_emit, isc, c->d_counters);
+                       c->em_idx, c->d_n_emit, isc, c->d_counters);
   else
     hipLaunchKernelGGL((k_emit_index<1, EmIdx>), dim3(eig), dim3(kEIThreads), 0, st, c->em_mask, lep->count,
-                     c->em_idx, c->d_n_emit, isc, c->d_counters);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const ScanDev sc{c->d_ticket, c->d_status};
-  const int recoil = (c->params.flags & QED_FLAG_NO_RECOIL) ? 0 : 1;
+                       c->em_idx, c->d_n_emit, isc, c->d_counters);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   // persistent workgroups: one per CU for the surrogate (its nets fill the LDS),
   // up to four per CU otherwise
   const int64_t wgs = use_mlp ? (int64_t)c->n_cu : 4 * (int64_t)c->n_cu;
   const unsigned grid = (unsigned)(ntiles < wgs ? ntiles : wgs);
-  const int64_t *dstep = step < 0 ? c->d_step : nullptr;
   if (use_mlp) {
-    EmitArgs<float> a{dev_species(lep), dev_species(ph), c->rad_lnh32, c->rad_S64, c->rad_q16,
-                      c->rad_s0sc, c->em_idx, (const EmRec<float> *)c->em_rec, c->d_n_emit,
-                      c->d_next_id, c->params.seed, c->params.kmax, recoil, (uint64_t)step, dstep, sc,
-                      c->d_counters, gen_mode(c), c->em_dt, c->range, retire_dev(c)};
+    EmitArgs<float> a = emit_args<float>(c, lep, ph, step, recoil, sc);
+    ScanClear clear{};
+    if (c->params.kmax > 1 && (e = clear_region(c, clear, 0, kRegEmitIndex, etiles)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_emit_mlp<false>, dim3(grid), dim3(kEmitMlpThreads), sizeof(EmitMlpLds), st, a, mlp_dev(c),
-                       c->em_mask, (const int32_t *)nullptr, (const int64_t *)nullptr);
+                       c->em_mask, (const int32_t *)nullptr, (const int64_t *)nullptr, clear);
     if (c->params.kmax > 1) {
       // the emitters with a further candidate (bits in the emitter mask, which
       // the list above no longer needs), listed in emitter order and finished
-      // in a second pass; both scan regions cleared again
-      hipLaunchKernelGGL(k_zero_scan2, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, c->d_ticket,
-                         c->d_status, c->status_len, n0, n1);
+      // in a second pass
       if (wide)
         hipLaunchKernelGGL((k_emit_index<8, int32_t>), dim3(eig), dim3(kEIThreads), 0, st, c->em_mask, c->d_n_emit,
                            c->cont_idx, c->d_n_cont, isc, c->d_counters);
       else
         hipLaunchKernelGGL((k_emit_index<1, int32_t>), dim3(eig), dim3(kEIThreads), 0, st, c->em_mask, c->d_n_emit,
                            c->cont_idx, c->d_n_cont, isc, c->d_counters);
+      a.sc = scan_region(c, kRegEmitCont);
       hipLaunchKernelGGL(k_emit_mlp<true>, dim3(grid), dim3(kEmitMlpThreads), sizeof(EmitMlpLds), st, a,
-                         mlp_dev(c), (uint64_t *)nullptr, c->cont_idx, c->d_n_cont);
+                         mlp_dev(c), (uint64_t *)nullptr, c->cont_idx, c->d_n_cont, ScanClear{});
     }
   } else if (lep->dtype == QED_F32) {
-    EmitArgs<float> a{dev_species(lep), dev_species(ph), c->rad_lnh32, c->rad_S64, c->rad_q16,
-                      c->rad_s0sc, c->em_idx, (const EmRec<float> *)c->em_rec, c->d_n_emit,
-                      c->d_next_id, c->params.seed, c->params.kmax, recoil, (uint64_t)step, dstep, sc,
-                      c->d_counters, gen_mode(c), c->em_dt, c->range, retire_dev(c)};
+    const EmitArgs<float> a = emit_args<float>(c, lep, ph, step, recoil, sc);
     if (a.gen) hipLaunchKernelGGL(k_emit_f32<true>, dim3(grid), dim3(emit_threads<float, true>()), 0, st, a);
     else hipLaunchKernelGGL(k_emit_f32<false>, dim3(grid), dim3(emit_threads<float, false>()), 0, st, a);
   } else {
-    EmitArgs<double> a{dev_species(lep), dev_species(ph), c->rad_lnh64, c->rad_S64, c->rad_q16,
-                       c->rad_s0sc, c->em_idx, (const EmRec<double> *)c->em_rec, c->d_n_emit,
-                       c->d_next_id, c->params.seed, c->params.kmax, recoil, (uint64_t)step, dstep, sc,
-                       c->d_counters, gen_mode(c), c->em_dt, c->range, retire_dev(c)};
+    const EmitArgs<double> a = emit_args<double>(c, lep, ph, step, recoil, sc);
     if (a.gen) hipLaunchKernelGGL(k_emit_f64<true>, dim3(grid), dim3(emit_threads<double, true>()), 0, st, a);
     else hipLaunchKernelGGL(k_emit_f64<false>, dim3(grid), dim3(emit_threads<double, false>()), 0, st, a);
   }
@@ -2311,13 +2514,13 @@ hipError_t launch_emit(qed_ctx *c, const qed_species_t *lep, const qed_species_t
 hipError_t launch_pairs(qed_ctx *c, const qed_fields_t *f, const qed_species_t *ph,
                         const qed_species_t *el, const qed_species_t *po, double dt, int64_t step,
                         hipStream_t st) {
-  const int64_t ntiles = (ph->capacity + kPairTile - 1) / kPairTile;
+  const bool small = ph->capacity <= kPairSmall;
+  const int64_t ptile = kPairThreads * (small ? 1 : 4), ntiles = (ph->capacity + ptile - 1) / ptile;
   const bool thin = (c->params.flags & QED_FLAG_SURROGATE) && ph->dtype == QED_F32;
-  if (ph->dtype != QED_F32) {   // (the float32 passes clear their scans themselves)
-    hipError_t e = zero_scan(c, ntiles, st);
-    if (e != hipSuccess) return e;
-  }
-  const ScanDev sc{c->d_ticket, c->d_status};
+  // float64: a region its kernel leaves clean; float32: the candidates' appends,
+  // cleared by the photon pass
+  const ScanDev sc = scan_region(c, ph->dtype == QED_F32 ? kRegPairCand : kRegClean);
+  if (ph->dtype != QED_F32 && ntiles > c->region_len[kRegClean]) return hipErrorInvalidValue;
   const int move = (c->params.flags & QED_FLAG_STATIC_PHOTONS) ? 0 : 1;
   const int64_t wgs = (int64_t)c->n_cu * 4;   // persistent, tiles from the ticket
   const unsigned grid = (unsigned)(ntiles < wgs ? ntiles : wgs);
@@ -2328,62 +2531,44 @@ hipError_t launch_pairs(qed_ctx *c, const qed_fields_t *f, const qed_species_t *
                       c->pair_S64, c->pair_q16, c->pair_s0sc, (float)dt, dt, move, c->d_next_id,
                       c->params.seed, (uint64_t)step, step < 0 ? c->d_step : nullptr, sc, c->d_counters, killed, c->range,
                       retire_dev(c)};
+    // streaming pass, event (candidate) list, events (candidates)
+    const bool wide = ph->capacity >= kEIWideFrom;
+    const int64_t eit = wide ? ei_tile<8>() : ei_tile<1>();
+    const int64_t etiles = (ph->capacity + eit - 1) / eit;
+    const unsigned eig = (unsigned)(etiles < 2 * (int64_t)c->n_cu ? etiles : 2 * (int64_t)c->n_cu);
+    const int64_t ctiles = (ph->capacity + kPCThreads - 1) / kPCThreads;
+    const ScanDev isc = scan_region(c, kRegPairIndex);
+    ScanClear clear{};
+    hipError_t e = clear_region(c, clear, 0, kRegPairIndex, etiles);
+    if (e == hipSuccess && thin) e = clear_region(c, clear, 1, kRegPairCand, ctiles);
+    if (e != hipSuccess) return e;
+    if (ph->capacity > c->cand_cap) return hipErrorInvalidValue;
+    const int64_t ttiles = (ph->capacity + kPTTile - 1) / kPTTile, twgs = (int64_t)c->n_cu * 8;
+    const dim3 tgrid((unsigned)(ttiles < twgs ? ttiles : twgs));
+    if (thin && a.ret.on)
+      hipLaunchKernelGGL(k_photon_thin<true>, tgrid, dim3(kPTThreads), 0, st, a, c->cand_mask, clear);
+    else if (thin)
+      hipLaunchKernelGGL(k_photon_thin<false>, tgrid, dim3(kPTThreads), 0, st, a, c->cand_mask, clear);
+    else if (f->kind == QED_FIELD_GRID)
+      hipLaunchKernelGGL(k_photon_table<QED_FIELD_GRID>, tgrid, dim3(kPTThreads), 0, st, a, c->cand_mask, clear);
+    else if (f->kind == QED_FIELD_UNIFORM)
+      hipLaunchKernelGGL(k_photon_table<QED_FIELD_UNIFORM>, tgrid, dim3(kPTThreads), 0, st, a, c->cand_mask, clear);
+    else
+      hipLaunchKernelGGL(k_photon_table<QED_FIELD_PER_PARTICLE>, tgrid, dim3(kPTThreads), 0, st, a, c->cand_mask,
+                         clear);
+    if (wide)
+      hipLaunchKernelGGL((k_emit_index<8, int32_t>), dim3(eig), dim3(kEIThreads), 0, st, c->cand_mask, ph->count,
+                         c->cand_idx, c->d_n_cand, isc, c->d_counters);
+    else
+      hipLaunchKernelGGL((k_emit_index<1, int32_t>), dim3(eig), dim3(kEIThreads), 0, st, c->cand_mask, ph->count,
+                         c->cand_idx, c->d_n_cand, isc, c->d_counters);
+    const int64_t ewgs = (int64_t)c->n_cu * 4;
+    const dim3 egrid((unsigned)(ctiles < ewgs ? ctiles : ewgs));
     if (thin) {
-      // thinning pass, candidate list, candidates (region 0 of the scan state
-      // for the candidates' appends, region 1 for the list)
-      const bool wide = ph->capacity >= kEIWideFrom;
-      const int64_t eit = wide ? ei_tile<8>() : ei_tile<1>();
-      const int64_t etiles = (ph->capacity + eit - 1) / eit;
-      const unsigned eig = (unsigned)(etiles < 2 * (int64_t)c->n_cu ? etiles : 2 * (int64_t)c->n_cu);
-      const int64_t ctiles = (ph->capacity + kPCThreads - 1) / kPCThreads;
-      const int64_t n0 = ctiles + 1, n1 = etiles + 1, nz = n0 > n1 ? n0 : n1;
-      if (nz > c->status_len || ph->capacity > c->cand_cap) return hipErrorInvalidValue;
-      hipLaunchKernelGGL(k_zero_scan2, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, c->d_ticket,
-                         c->d_status, c->status_len, n0, n1);
-      const int64_t ttiles = (ph->capacity + kPTTile - 1) / kPTTile, twgs = (int64_t)c->n_cu * 8;
-      const unsigned tgrid = (unsigned)(ttiles < twgs ? ttiles : twgs);
-      if (a.ret.on)
-        hipLaunchKernelGGL(k_photon_thin<true>, dim3(tgrid), dim3(kPTThreads), 0, st, a, c->cand_mask);
-      else
-        hipLaunchKernelGGL(k_photon_thin<false>, dim3(tgrid), dim3(kPTThreads), 0, st, a, c->cand_mask);
-      const ScanDev isc{c->d_ticket + 1, c->d_status + c->status_len};
-      if (wide)
-        hipLaunchKernelGGL((k_emit_index<8, int32_t>), dim3(eig), dim3(kEIThreads), 0, st, c->cand_mask,
-                           ph->count, c->cand_idx, c->d_n_cand, isc, c->d_counters);
-      else
-        hipLaunchKernelGGL((k_emit_index<1, int32_t>), dim3(eig), dim3(kEIThreads), 0, st, c->cand_mask,
-                           ph->count, c->cand_idx, c->d_n_cand, isc, c->d_counters);
-      const int64_t cwgs = (int64_t)c->n_cu * 4;
-      hipLaunchKernelGGL(k_pair_cand, dim3((unsigned)(ctiles < cwgs ? ctiles : cwgs)), dim3(kPCThreads), 0, st, a,
-                         c->cand_idx, c->d_n_cand, c->mlp_theta[1], c->params.kmax);
+      hipLaunchKernelGGL(k_pair_cand, egrid, dim3(kPCThreads), 0, st, a, c->cand_idx, c->d_n_cand, c->mlp_theta[1],
+                         c->params.kmax);
     } else {
-      // streaming pass, event list (region 1 of the scan state), events, counts
-      const bool wide = ph->capacity >= kEIWideFrom;
-      const int64_t eit = wide ? ei_tile<8>() : ei_tile<1>();
-      const int64_t etiles = (ph->capacity + eit - 1) / eit;
-      const unsigned eig = (unsigned)(etiles < 2 * (int64_t)c->n_cu ? etiles : 2 * (int64_t)c->n_cu);
-      if (etiles + 1 > c->status_len || ph->capacity > c->cand_cap) return hipErrorInvalidValue;
-      hipLaunchKernelGGL(k_zero_scan2, dim3((unsigned)((etiles + 1 + 255) / 256)), dim3(256), 0, st, c->d_ticket,
-                         c->d_status, c->status_len, (int64_t)1, etiles + 1);
-      const int64_t ttiles = (ph->capacity + kPTTile - 1) / kPTTile, twgs = (int64_t)c->n_cu * 8;
-      const unsigned tgrid = (unsigned)(ttiles < twgs ? ttiles : twgs);
-      if (f->kind == QED_FIELD_GRID)
-        hipLaunchKernelGGL(k_photon_table<QED_FIELD_GRID>, dim3(tgrid), dim3(kPTThreads), 0, st, a, c->cand_mask);
-      else if (f->kind == QED_FIELD_UNIFORM)
-        hipLaunchKernelGGL(k_photon_table<QED_FIELD_UNIFORM>, dim3(tgrid), dim3(kPTThreads), 0, st, a, c->cand_mask);
-      else
-        hipLaunchKernelGGL(k_photon_table<QED_FIELD_PER_PARTICLE>, dim3(tgrid), dim3(kPTThreads), 0, st, a,
-                           c->cand_mask);
-      const ScanDev isc{c->d_ticket + 1, c->d_status + c->status_len};
-      if (wide)
-        hipLaunchKernelGGL((k_emit_index<8, int32_t>), dim3(eig), dim3(kEIThreads), 0, st, c->cand_mask,
-                           ph->count, c->cand_idx, c->d_n_cand, isc, c->d_counters);
-      else
-        hipLaunchKernelGGL((k_emit_index<1, int32_t>), dim3(eig), dim3(kEIThreads), 0, st, c->cand_mask,
-                           ph->count, c->cand_idx, c->d_n_cand, isc, c->d_counters);
-      const int64_t ewgs = (int64_t)c->n_cu * 4, eblocks = (ph->capacity + 255) / 256;
-      hipLaunchKernelGGL(k_pair_events, dim3((unsigned)(eblocks < ewgs ? eblocks : ewgs)), dim3(256), 0, st, a,
-                         c->cand_idx, c->d_n_cand);
+      hipLaunchKernelGGL(k_pair_events, egrid, dim3(kPCThreads), 0, st, a, c->cand_idx, c->d_n_cand);
       hipLaunchKernelGGL(k_pair_commit, dim3(1), dim3(1), 0, st, a, c->d_n_cand);
     }
   } else {
@@ -2391,13 +2576,18 @@ hipError_t launch_pairs(qed_ctx *c, const qed_fields_t *f, const qed_species_t *
                        c->pair_S64, c->pair_q16, c->pair_s0sc, dt, dt, move, c->d_next_id,
                        c->params.seed, (uint64_t)step, step < 0 ? c->d_step : nullptr, sc, c->d_counters, killed, c->range,
                       retire_dev(c)};
-    hipLaunchKernelGGL(k_pairs_f64, dim3(grid), dim3(kPairThreads), 0, st, a);
+    if (small) hipLaunchKernelGGL(k_pairs_f64<1>, dim3(grid), dim3(kPairThreads), 0, st, a);
+    else hipLaunchKernelGGL(k_pairs_f64<4>, dim3(grid), dim3(kPairThreads), 0, st, a);
   }
   return hipGetLastError();
 }
 
+static hipError_t launch_compact_at(qed_ctx *c, const qed_species_t *sp, const ScanDev &sc, hipStream_t st);
+
 hipError_t launch_compact(qed_ctx *c, const qed_species_t *sp, hipStream_t st) {
-  return launch_compact_scan(c, sp, c->d_ticket, c->d_status, c->status_len, st);
+  const ScanDev sc = scan_region(c, kRegClean);
+  if ((sp->capacity + kCTile - 1) / kCTile > c->region_len[kRegClean]) return hipErrorInvalidValue;
+  return launch_compact_at(c, sp, sc, st);
 }
 
 static_assert(kCTile == kCompactTile, "compaction tile size of the scan-state bound");
@@ -2406,8 +2596,12 @@ hipError_t launch_compact_scan(qed_ctx *c, const qed_species_t *sp, uint32_t *ti
                                int64_t status_len, hipStream_t st) {
   const int64_t ntiles = (sp->capacity + kCTile - 1) / kCTile;
   hipError_t e = zero_scan_at(ticket, status, status_len, ntiles, st);
-  if (e != hipSuccess) return e;
-  const ScanDev sc{ticket, status};
+  return e == hipSuccess ? launch_compact_at(c, sp, ScanDev{ticket, status}, st) : e;
+}
+
+static hipError_t launch_compact_at(qed_ctx *c, const qed_species_t *sp, const ScanDev &sc, hipStream_t st) {
+  const int64_t ntiles = (sp->capacity + kCTile - 1) / kCTile;
+  hipError_t e = hipSuccess;
   const bool track = (c->params.flags & QED_FLAG_TRACK_DEAD) != 0;
   const bool owner = track && c->killed_owner == sp->x;
   int64_t *killed = owner ? c->d_killed : nullptr;

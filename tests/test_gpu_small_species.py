@@ -1,0 +1,92 @@
+"""Kernels chosen for small species against the general ones: the same particles
+in a species whose capacity takes either side of the rule give the same photons
+and pairs.  The two compile the same device functions, so ids, counts and order
+are equal and values agree to a few roundings of their type (an event's dozen
+float32 or float64 operations in a row: 64 units in the last place)."""
+import math
+
+import numpy as np
+import pytest
+
+from tests.gpu_helpers import need_gpu
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+SMALL, LARGE = 1 << 17, (1 << 17) + 1              # capacities either side of the emission's rule
+PAIR_SMALL, PAIR_LARGE = 1 << 18, (1 << 18) + 1    # and of the float64 pair pass's
+ULPS = {"f32": 64 * 2.0 ** -24, "f64": 64 * 2.0 ** -53}
+
+
+def _same(a, b, dtype):
+    assert np.array_equal(a["id"], b["id"])
+    for k in ("x", "p"):
+        scale = np.maximum(np.abs(b[k]), np.abs(b[k]).max(axis=1, keepdims=True)) if b[k].size else b[k]
+        assert np.all(np.abs(a[k] - b[k]) <= ULPS[dtype] * scale)
+    # the optical depth: a float64 draw, less a rate of the species' precision
+    assert np.all(np.abs(a["tau"] - b["tau"]) <= ULPS[dtype] * np.maximum(1.0, np.abs(b["tau"])))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("method1", [False, True])
+@pytest.mark.parametrize("n,dt", [(0, 0.01), (1, 2.0), (255, 2.0), (256, 0.01), (257, 2.0), (5000, 0.01), (5000, 2.0),
+                                  (SMALL, 0.02)])
+def test_emission_small_equals_list(dtype, method1, n, dt):
+    """dt = 2: nearly every electron emits, so tiles are full and the cap is
+    reached; 0.01: a few emitters per tile."""
+    torch, q = need_gpu()
+    ens = workloads.uniform_b_ensembles(max(n, 1), seed=5, triples=((2000.0, 206.0),))[0]
+    out = []
+    for cap in (SMALL, LARGE):
+        ctx = q.Context(seed=9, kmax=4, flags=q.QED_FLAG_METHOD_I if method1 else 0)
+        ctx.qed_build_tables(q.QED_FORMULA_I)
+        lep, ph = q.Species(cap, dtype), q.Species(12 * max(n, 1), dtype)
+        lep.load(ens["x"][:n], ens["p"][:n], np.zeros(n), ens["id"][:n])
+        ctx.qed_init_optical_depth(lep, 0)
+        ctx.qed_set_next_id(n)
+        fld = q.Fields(q.QED_FIELD_UNIFORM, B=(0, 0, 2000.0))
+        print(f"emission: {dtype} method1={method1} n={n} dt={dt} capacity {cap}", flush=True)
+        for s in range(3):
+            ctx.qed_gather_push(fld, lep, -1, dt, s)
+            ctx.qed_emit_photons(lep, ph, s)
+        st, _ = ctx.qed_get_status()
+        out.append((lep.to_numpy(), ph.to_numpy(), st))
+        ctx.close()
+    (la, pa, sa), (lb, pb, sb) = out
+    assert sa == sb
+    assert sa["photons"] == pa["id"].size and (n < 200 or sa["photons"] > 0)
+    _same(la, lb, dtype)
+    _same(pa, pb, dtype)
+
+
+@pytest.mark.parametrize("n", [0, 1, 255, 257, 20000, PAIR_SMALL])
+def test_pairs_f64_one_and_four_photons_per_thread(n):
+    torch, q = need_gpu()
+    w = workloads.pair_photons(max(n, 1), seed=6, chi_lo=1.0)
+    perp = np.linalg.norm(np.cross(w["khat"], w["E"] + np.cross(w["khat"], w["B"])), axis=1)
+    k = w["khat"] * (w["chi_target"] * (510998.95 / 1.239841984) / perp)[:, None]
+    out = []
+    for cap in (PAIR_SMALL, PAIR_LARGE):
+        ctx = q.Context(seed=2, kmax=4, flags=q.QED_FLAG_TRACK_DEAD)
+        ctx.qed_build_tables(q.QED_FORMULA_I)
+        ph, el, po = q.Species(cap, "f64"), q.Species(max(n, 1), "f64"), q.Species(max(n, 1), "f64")
+        ph.load(w["x"][:n], k[:n], np.zeros(n), w["id"][:n])
+        e0 = np.zeros((0, 3))
+        for sp in (el, po):
+            sp.load(e0, e0, np.zeros(0), np.zeros(0, np.uint64))
+        ctx.qed_init_optical_depth(ph, 0)
+        ctx.qed_set_next_id(n)
+        fld = q.Fields(q.QED_FIELD_UNIFORM, E=(100.0, -50.0, 30.0), B=(0, 0, 2000.0))
+        print(f"pairs f64: n={n} capacity {cap}", flush=True)
+        for s in range(3):
+            ctx.qed_create_pairs(fld, ph, el, po, 0.02, s)
+            ctx.qed_compact(ph)
+        st, _ = ctx.qed_get_status()
+        out.append(([sp.to_numpy() for sp in (ph, el, po)], st))
+        ctx.close()
+    (a, sa), (b, sb) = out
+    assert sa == sb
+    assert sa["pairs"] == a[1]["id"].size and (n < 1000 or sa["pairs"] > 0)
+    for x, y in zip(a, b):
+        _same(x, y, "f64")
