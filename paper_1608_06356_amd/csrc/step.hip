@@ -159,12 +159,14 @@ __device__ __forceinline__ void gather_grid(const FieldDev &f, R x, R y, R z, R 
 // (the span of their centre nodes, one node wider on each side) into LDS once
 // and every particle reads its 27 nodes from there, which cuts the bytes the
 // vector L1 returns per particle from 27 x 24 to about the box's share.  A
-// workgroup whose box exceeds kBoxCap nodes gathers from global memory.
-constexpr int kBoxCap = 1024;
-constexpr int kGPWaves = 6;     // LDS allows 6 workgroups of 256 threads per CU
+// workgroup whose box exceeds its capacity gathers from global memory.
+// 4 T nodes for T threads: the LDS allows 24 waves per CU whatever T.
+constexpr int kGPWaves = 6;
 
+template <int T>
 struct BoxLds {
-  float2 node[kBoxCap * 3];     // 6 floats per node; node (x, y, z) at z * pxy + y * px + x
+  static constexpr int kCap = 4 * T;
+  float2 node[kCap * 3];        // 6 floats per node; node (x, y, z) at z * pxy + y * px + x
   int ref[3];                   // centre node of the workgroup's first particle
   int lo[3], hi[3];             // extremes of the centre nodes relative to ref
   int bad;                      // a particle's stencil left the box (then: global gather)
@@ -202,10 +204,10 @@ __device__ __forceinline__ int row_extreme(int v) {
 // particle it, with stencil centre j[it].  On success the box is in LDS, rel holds the
 // thread's stencil corner (node j-1) in box coordinates and pit the row and
 // plane pitches (odd, which spreads neighbouring rows and planes over the LDS
-// banks).  Returns false (uniformly) when the box exceeds kBoxCap nodes.  Its
+// banks).  Returns false (uniformly) when the box exceeds BoxLds<T>::kCap nodes.  Its
 // first barrier also publishes whatever the caller wrote to LDS before.
-template <int IT>
-__device__ __forceinline__ bool stage_box(BoxLds &S, const FieldDev &f, const bool live[IT], const int j[IT][3],
+template <int IT, int T>
+__device__ __forceinline__ bool stage_box(BoxLds<T> &S, const FieldDev &f, const bool live[IT], const int j[IT][3],
                                           int rel[IT][3], int pit[2]) {
   const int n3[3] = {f.nx, f.ny, f.nz};
   int jj[IT][3];
@@ -244,7 +246,7 @@ __device__ __forceinline__ bool stage_box(BoxLds &S, const FieldDev &f, const bo
     bdim[d] = h - l + 3;
   }
   const int px = bdim[0] | 1, pxy = (px * bdim[1]) | 1;
-  if ((int64_t)pxy * bdim[2] > kBoxCap) return false;
+  if ((int64_t)pxy * bdim[2] > S.kCap) return false;
   // copy the box: node p of the dense enumeration (x fastest) -> (x, y, z).
   // The quotients use the hardware reciprocal (relative error below 2^-22):
   // (p + 0.5) / d is at least 0.5 / d <= 2^-11 away from an integer and below
@@ -264,7 +266,7 @@ __device__ __forceinline__ bool stage_box(BoxLds &S, const FieldDev &f, const bo
   if (inside) {
     const uint32_t sy6 = (uint32_t)f.nx * 6u, sz6 = (uint32_t)f.nx * (uint32_t)f.ny * 6u;
     const float *gb = f.grid + (uint32_t)g0[2] * sz6 + (uint32_t)g0[1] * sy6 + (uint32_t)g0[0] * 6u;
-    for (int p = threadIdx.x; p < cnt; p += kGPThreads) {
+    for (int p = threadIdx.x; p < cnt; p += T) {
       const uint32_t z = (uint32_t)(((float)p + 0.5f) * inv_bxy);
       const uint32_t q = (uint32_t)p - __umul24(z, (uint32_t)bxy);
       const uint32_t y = (uint32_t)(((float)q + 0.5f) * inv_bx);
@@ -277,7 +279,7 @@ __device__ __forceinline__ bool stage_box(BoxLds &S, const FieldDev &f, const bo
       d[0] = v0; d[1] = v1; d[2] = v2;
     }
   } else {
-    for (int p = threadIdx.x; p < cnt; p += kGPThreads) {
+    for (int p = threadIdx.x; p < cnt; p += T) {
       const int z = (int)(((float)p + 0.5f) * inv_bxy);
       const int q = p - (int)__umul24((uint32_t)z, (uint32_t)bxy);
       const int y = (int)(((float)q + 0.5f) * inv_bx);
@@ -317,8 +319,8 @@ __device__ __forceinline__ bool stage_box(BoxLds &S, const FieldDev &f, const bo
 // pitches with adds only.  DB: the next row's reads are issued before the
 // current row's products, so that LDS latency overlaps the arithmetic (18 more
 // registers); without it the other waves of the SIMD hide that latency.
-template <typename R, bool DB = true>
-__device__ __forceinline__ void gather_box(const BoxLds &S, const int c0[3], const int pit[2], const R w[3][3],
+template <typename R, bool DB = true, int T>
+__device__ __forceinline__ void gather_box(const BoxLds<T> &S, const int c0[3], const int pit[2], const R w[3][3],
                                            R F[6]) {
 #pragma unroll
   for (int c = 0; c < 6; ++c) F[c] = (R)0;
@@ -737,14 +739,14 @@ __device__ __forceinline__ void gp_finish(const GPArgs<R> &a, const GPTile<R> &P
 // optical depth runs down at the envelope rate h_rad_env (Poisson thinning);
 // the emission pass evaluates the rate net only at the candidate events this
 // finds and keeps each with probability W / W_env.
-template <typename R, int FK, bool M1, bool Thin = false>
-__global__ __launch_bounds__(kGPThreads, (gp_waves<R, FK, M1>())) void k_gather_push(GPArgs<R> a) {
+template <typename R, int FK, bool M1, bool Thin = false, int T = kGPThreads>
+__global__ __launch_bounds__(T, (gp_waves<R, FK, M1>())) void k_gather_push(GPArgs<R> a) {
   __shared__ R lnh_s[kRadNChi];
   // (the grid is sized by the capacity: blocks beyond the particles present
   // return, and they are the last ones dispatched)
   const int64_t n = *a.sp.count;
   scan_clear(a.clear);
-  const int64_t base = gp_tile_base(kGPThreads);
+  const int64_t base = gp_tile_base(T);
   if (base >= n) return;
   const int t = threadIdx.x;
   const int64_t i = base + t;
@@ -763,12 +765,12 @@ __global__ __launch_bounds__(kGPThreads, (gp_waves<R, FK, M1>())) void k_gather_
   for (int q = threadIdx.x; q < kRadNChi; q += blockDim.x) lnh_s[q] = a.lnh[q];
   R F[6];
   if (FK == QED_FIELD_GRID) {
-    __shared__ BoxLds box_s;
+    __shared__ BoxLds<T> box_s;
     int j[1][3], rel[1][3], pit[2];
     R w[3][3];
     tsc_setup<R>(f, x, y, z, j[0], w);      // dead lanes hold x = 0: harmless, unused
-    if (stage_box<1>(box_s, f, &live, j, rel, pit)) {   // its barriers also publish lnh_s
-      if (live) gather_box<R>(box_s, rel[0], pit, w, F);
+    if (stage_box<1, T>(box_s, f, &live, j, rel, pit)) {   // its barriers also publish lnh_s
+      if (live) gather_box<R, true>(box_s, rel[0], pit, w, F);
     } else {
       if (live) gather_global<R>(f, j[0], w, F);
       if (threadIdx.x == 0) atomicAdd(&counter_slot(a.counters)[cBoxFallback], 1ull);
@@ -787,15 +789,25 @@ __global__ __launch_bounds__(kGPThreads, (gp_waves<R, FK, M1>())) void k_gather_
 // is shared by 512 particles.  A sparse species' 512 particles span too many
 // cells for one box, so it keeps the kernel above.
 constexpr int64_t kDenseGP = 64;
+
+// Species with few particles per cell (below kSparseGP, and at least kSparseMin in
+// all, so that the workgroups still fill the GPU) take workgroups of 512 threads
+// with a box of 2048 nodes: 256 such particles spread over so many cells that late
+// in a sort interval 43 % of the workgroups' boxes exceed 1024 nodes (1e7 electrons
+// on 128^3).  A re-sort interval of 12 steps with 256 / 512 threads: 5e6 electrons
+// on 128^3 (2.4 per cell) 3.34 / 3.09 ms, 2e6 on 96^3 (2.3) 1.60 / 1.52, of 15
+// steps 1e7 on 128^3 (4.8) 6.19 / 6.06; above, the boxes fit and the larger
+// workgroup's barriers cost more: 5e6 on 96^3 (5.7) 2.36 / 2.50.
+constexpr int64_t kSparseGP = 5, kSparseMin = (int64_t)1 << 19;
 template <bool Thin>
 __global__ __launch_bounds__(kGPThreads, kGPWaves) void k_gather_push2(GPArgs<float> a) {
   using R = float;
-  constexpr int IT = 2;
+  constexpr int IT = 2, T = kGPThreads;
   __shared__ R lnh_s[kRadNChi];
-  __shared__ BoxLds box_s;
+  __shared__ BoxLds<T> box_s;
   const int64_t n = *a.sp.count;
   scan_clear(a.clear);
-  const int64_t base = gp_tile_base((int64_t)kGPThreads * IT);
+  const int64_t base = gp_tile_base((int64_t)T * IT);
   if (base >= n) return;
   const int t = threadIdx.x;
   FieldDev f = a.f;
@@ -806,7 +818,7 @@ __global__ __launch_bounds__(kGPThreads, kGPWaves) void k_gather_push2(GPArgs<fl
   const GPTile<R> P(a.sp, base);
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
-    const int o = it * kGPThreads + t;
+    const int o = it * T + t;
     live[it] = base + o < n;
     xs[it][0] = live[it] ? P.x[o] : (R)0; xs[it][1] = live[it] ? P.y[o] : (R)0; xs[it][2] = live[it] ? P.z[o] : (R)0;
   }
@@ -818,7 +830,7 @@ __global__ __launch_bounds__(kGPThreads, kGPWaves) void k_gather_push2(GPArgs<fl
     R w[3][3];
     tsc_setup<R>(f, xs[it][0], xs[it][1], xs[it][2], j[it], w);   // dead particles hold x = 0: unused
   }
-  const bool boxed = stage_box<IT>(box_s, f, live, j, rel, pit);   // its barriers also publish lnh_s
+  const bool boxed = stage_box<IT, T>(box_s, f, live, j, rel, pit);   // its barriers also publish lnh_s
   if (!boxed && threadIdx.x == 0) atomicAdd(&counter_slot(a.counters)[cBoxFallback], 1ull);
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
@@ -828,7 +840,7 @@ __global__ __launch_bounds__(kGPThreads, kGPWaves) void k_gather_push2(GPArgs<fl
     // 72 registers, which six waves per SIMD allow (the LDS allows six
     // workgroups per CU); holding any of these through the staging or a second
     // row in flight needs more and measured slower
-    const int o = it * kGPThreads + t;
+    const int o = it * T + t;
     R px = 0, py = 0, pz = 0;
     double tau = 0.0;
     if (live[it]) { px = P.px[o]; py = P.py[o]; pz = P.pz[o]; tau = P.tau[o]; }
@@ -2318,8 +2330,7 @@ static hipError_t clear_region(const qed_ctx *c, ScanClear &cl, int at, int k, i
 // Blocks of a gather/push launch for a species of this capacity, IT particles
 // per thread: every tile has its block (chunks per XCD, times the chunk, times
 // the 8 XCDs).
-static unsigned gp_grid(int64_t capacity, int it) {
-  const int64_t tile = (int64_t)kGPThreads * it;
+static unsigned gp_grid(int64_t capacity, int64_t tile) {
   const int64_t ntiles = (capacity + tile - 1) / tile;
   const int64_t cpx = ((ntiles + kGPChunk - 1) / kGPChunk + kXcds - 1) / kXcds;
   return (unsigned)(cpx * kGPChunk * kXcds);
@@ -2336,17 +2347,21 @@ static void launch_gp_kind_m(const GPArgs<R> &a, int kind, int64_t cap, bool den
   if (kind == QED_FIELD_GRID) {
     if constexpr (sizeof(R) == 4 && !M1) {
       if (dense) {
-        hipLaunchKernelGGL((k_gather_push2<Thin>), dim3(gp_grid(cap, 2)), dim3(kGPThreads), 0, st, a);
+        hipLaunchKernelGGL((k_gather_push2<Thin>), dim3(gp_grid(cap, 2 * kGPThreads)), dim3(kGPThreads), 0, st, a);
+        return;
+      }
+      if (cap >= kSparseMin && cap < kSparseGP * (int64_t)a.f.nx * a.f.ny * a.f.nz) {
+        hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_GRID, M1, Thin, 512>), dim3(gp_grid(cap, 512)), dim3(512), 0, st, a);
         return;
       }
     }
-    hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_GRID, M1, Thin>), dim3(gp_grid(cap, 1)), dim3(kGPThreads), 0, st,
+    hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_GRID, M1, Thin>), dim3(gp_grid(cap, kGPThreads)), dim3(kGPThreads), 0, st,
                        a);
   } else if (kind == QED_FIELD_UNIFORM) {
-    hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_UNIFORM, M1, Thin>), dim3(gp_grid(cap, 1)), dim3(kGPThreads), 0,
+    hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_UNIFORM, M1, Thin>), dim3(gp_grid(cap, kGPThreads)), dim3(kGPThreads), 0,
                        st, a);
   } else {
-    hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_PER_PARTICLE, M1, Thin>), dim3(gp_grid(cap, 1)),
+    hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_PER_PARTICLE, M1, Thin>), dim3(gp_grid(cap, kGPThreads)),
                        dim3(kGPThreads), 0, st, a);
   }
 }

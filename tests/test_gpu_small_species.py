@@ -90,3 +90,48 @@ def test_pairs_f64_one_and_four_photons_per_thread(n):
     assert sa["pairs"] == a[1]["id"].size and (n < 1000 or sa["pairs"] > 0)
     for x, y in zip(a, b):
         _same(x, y, "f64")
+
+
+@pytest.mark.parametrize("order", ["sorted", "random"])
+@pytest.mark.parametrize("n", [600_001, 513])
+def test_wide_workgroups_of_a_sparse_species(order, n):
+    """The 512-thread lepton pass (fewer than five particles per cell, capacity of
+    at least 2^19) against the 256-thread one (a larger capacity): the same
+    emitters and photons, values to float32 rounding (positions within 2 units in
+    the last place of the box length, momenta within 16 of the larger of |p| and
+    the kick a0 dt, optical depths within the rate's 1e-6), from staged boxes
+    and from the global gather."""
+    torch, q = need_gpu()
+    ng, L, dt, a0 = 64, workloads.BOX_L, 0.01, 500.0
+    ens = workloads.standing_wave_electrons(n, seed=8)
+    tau = np.random.default_rng(1).exponential(size=n)
+    grid = torch.empty(ng ** 3 * 6, dtype=torch.float32, device="cuda")
+    fld = q.Fields(q.QED_FIELD_GRID, grid=grid, n=ng, L=L)
+    out = []
+    for cap in (600_001, 5 * ng ** 3):
+        print(f"sparse lepton pass: n={n} {order} capacity {cap}", flush=True)
+        ctx = q.Context(seed=3, kmax=4)
+        ctx.qed_build_tables(q.QED_FORMULA_I)
+        ctx.qed_fill_standing_wave(grid, ng, L, a0, 0.21)
+        src, lep, ph = q.Species(cap, "f32"), q.Species(cap, "f32"), q.Species(200_000, "f32")
+        src.load(ens["x"], ens["p"], tau, ens["id"])
+        if order == "sorted":
+            ctx.qed_sort_by_cell(fld, src, lep)
+        else:
+            lep = src
+        ctx.qed_set_next_id(n)
+        ctx.qed_gather_push(fld, lep, -1, dt, 0)
+        ctx.qed_emit_photons(lep, ph, 0)
+        st, _ = ctx.qed_get_status()
+        out.append((lep.to_numpy(), ph.to_numpy(), st))
+        ctx.close()
+    (a, pa, sa), (b, pb, sb) = out
+    assert sa["events"] == sb["events"] > 0
+    if n > 1000:            # (tiles that straddle two distant blocks fall back in cell order too)
+        tiles = -(-n // 512)
+        assert sa["box_fallback"] == tiles if order == "random" else sa["box_fallback"] < tiles // 2
+    assert np.array_equal(a["id"], b["id"]) and np.array_equal(pa["id"], pb["id"])
+    assert np.max(np.abs(a["x"] - b["x"])) <= 2.0 ** -20
+    assert np.max(np.abs(a["p"] - b["p"]) / np.maximum(np.abs(b["p"]), a0 * dt)) <= 2.0 ** -19
+    np.testing.assert_allclose(a["tau"], b["tau"], rtol=1e-6, atol=1e-6)
+    np.testing.assert_allclose(pa["p"], pb["p"], rtol=1e-5, atol=1e-4)
