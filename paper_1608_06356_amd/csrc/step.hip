@@ -1927,12 +1927,11 @@ __global__ __launch_bounds__(kPCThreads) void k_pair_cand(PairArgs<float> a, con
 // k_pair_commit advances the counts.  The streaming kernel has no scan, so its
 // workgroups do not wait on each other; the events (a few per thousand photons)
 // are handled one per thread.
-// FK: the field kind (a.f.kind), a template parameter so that each kind keeps
-// only its own field code and registers: at most 128 (four waves per SIMD),
-// 168 on a grid (three waves: its four 27-node gathers in flight).
-template <int FK> constexpr int pt_waves() { return FK == QED_FIELD_GRID ? 3 : 4; }
+// FK: the field kind (a.f.kind, uniform or per particle), a template parameter so
+// that each kind keeps only its own field code and registers: at most 128 (four
+// waves per SIMD).
 template <int FK>
-__global__ __launch_bounds__(kPTThreads, (pt_waves<FK>())) void k_photon_table(PairArgs<float> a, uint64_t *emask,
+__global__ __launch_bounds__(kPTThreads, 4) void k_photon_table(PairArgs<float> a, uint64_t *emask,
                                                                                    ScanClear clear) {
   __shared__ float L_s[kPairNRate];
   __shared__ uint32_t cnt_s[cNumCounters];
@@ -1944,7 +1943,7 @@ __global__ __launch_bounds__(kPTThreads, (pt_waves<FK>())) void k_photon_table(P
   const int64_t n = *a.ph.count;
   float *X = (float *)a.ph.x, *Y = (float *)a.ph.y, *Z = (float *)a.ph.z;
   const float *KX = (const float *)a.ph.px, *KY = (const float *)a.ph.py, *KZ = (const float *)a.ph.pz;
-  const bool need_x = a.move || FK == QED_FIELD_GRID;
+  const bool need_x = a.move;
   constexpr bool pp = FK == QED_FIELD_PER_PARTICLE;
   const double t_left = time_left(a.ret, step_of(a.step, a.d_step), a.dtd);
   uint32_t nrange = 0, nnan = 0, nret = 0;
@@ -1980,10 +1979,6 @@ __global__ __launch_bounds__(kPTThreads, (pt_waves<FK>())) void k_photon_table(P
         if (a.move && gph > 0.f) {
           const float vdt = rcp<float>(gph) * a.dt;
           x += kx * vdt; y += ky * vdt; z += kz * vdt;
-          if (a.f.kind == QED_FIELD_GRID) {
-            wrap_coord<float>(x, box_len<float>(a.f, 0)); wrap_coord<float>(y, box_len<float>(a.f, 1));
-            wrap_coord<float>(z, box_len<float>(a.f, 2));
-          }
           X[i] = x; Y[i] = y; Z[i] = z;
         }
         double chi, W;
@@ -2009,6 +2004,88 @@ __global__ __launch_bounds__(kPTThreads, (pt_waves<FK>())) void k_photon_table(P
   count_flush(cnt_s, a.counters);
   // retired photons are dead too: the compaction of this species must not skip
   if (threadIdx.x == 0 && a.killed && cnt_s[cRetired])
+    atomicAdd((unsigned long long *)a.killed, (unsigned long long)cnt_s[cRetired]);
+}
+
+// The same on a grid, and (Thin) the surrogate's pass with the envelope at the
+// photon's own chi.  Photons appear in the order of the leptons that emitted them
+// and are sorted with them, so a workgroup's photons lie close together and stage
+// the box of their stencils in LDS as the lepton pass does (stage_box); one whose
+// box is too large gathers from global memory, which cost every photon 27 scattered
+// reads.  Tiles are dealt to the XCDs in chunks (gp_tile_base).  One photon per
+// thread: two share a box but need 128 registers.  Five waves per SIMD (six take 66
+// registers and lose where boxes fall back).  Intervals of the table cascade: 3e6
+// electrons on 32^3 6.29 -> 4.61 ms, 1e7 on 64^3 18.9 -> 13.5, 5e6 on 128^3 16.5 ->
+// 13.6, 1e5 on 32^3 1.60 -> 1.33 (there one photon per thread counts, not four).
+template <bool Thin>
+__global__ __launch_bounds__(kGPThreads, 5) void k_photon_grid(PairArgs<float> a, uint64_t *emask, ScanClear clear) {
+  constexpr int T = kGPThreads;
+  __shared__ BoxLds<T> box_s;
+  __shared__ float L_s[kPairNRate];
+  __shared__ uint32_t cnt_s[cNumCounters];
+  scan_clear(clear);
+  const int64_t n = *a.ph.count, base = gp_tile_base(T);
+  if (base >= n) return;
+  const int t = threadIdx.x;
+  const int64_t i = base + t;
+  FieldDev f = a.f;
+  f.kind = QED_FIELD_GRID;
+  const GPTile<float> P(a.ph, base);
+  count_zero(cnt_s);
+  // present: in the species; alive: not converted (a converted photon not yet
+  // compacted away keeps its place, and its position, in the box)
+  const bool present = i < n;
+  bool alive = false;
+  float kx = 0.f, ky = 0.f, kz = 0.f, x = 0.f, y = 0.f, z = 0.f;
+  double tau = 0.0;
+  if (present) {
+    alive = a.ph.id[i] != kDeadId;
+    kx = P.px[t]; ky = P.py[t]; kz = P.pz[t];
+    x = P.x[t]; y = P.y[t]; z = P.z[t];
+    tau = P.tau[t];
+  }
+  if (!Thin)
+    for (int k = t; k < kPairNRate; k += T) L_s[k] = a.L[k];
+  const float gph = root<float>(kx * kx + ky * ky + kz * kz);
+  if (a.move && alive && gph > 0.f) {
+    const float vdt = rcp<float>(gph) * a.dt;
+    x += kx * vdt; y += ky * vdt; z += kz * vdt;
+    wrap_coord<float>(x, box_len<float>(f, 0)); wrap_coord<float>(y, box_len<float>(f, 1));
+    wrap_coord<float>(z, box_len<float>(f, 2));
+    P.x[t] = x; P.y[t] = y; P.z[t] = z;
+  }
+  int j[1][3], rel[1][3], pit[2];
+  float w[3][3], F[6];
+  tsc_setup<float>(f, x, y, z, j[0], w);      // absent lanes hold x = 0: harmless, unused
+  if (stage_box<1, T>(box_s, f, &present, j, rel, pit)) {   // its barriers also publish L_s and cnt_s
+    if (alive) gather_box<float>(box_s, rel[0], pit, w, F);
+  } else {
+    if (alive) gather_global<float>(f, j[0], w, F);
+  }
+  uint32_t nrange = 0, nnan = 0, nret = 0;
+  bool ev = false;
+  if (alive) {
+    double chi, W = 0.0;
+    if constexpr (Thin) {
+      chi = fields_finite<float>(F) ? chi_photon_f32(kx, ky, kz, F) : NAN;
+      if (isfinite(chi)) W = photon_envelope(a, chi, gph);
+    } else {
+      photon_rate_at<float>(a, L_s, F, kx, ky, kz, gph, chi, W);
+    }
+    if (isfinite(chi)) nrange += chi > a.rg.pair_hi;
+    else ++nnan;
+    ev = W > 0.0 && tau <= W * a.dtd;
+    if (!ev)
+      photon_settle(a, i, tau - W * a.dtd, gph, time_left(a.ret, step_of(a.step, a.d_step), a.dtd), nret);
+  }
+  const uint64_t bal = __ballot(ev);
+  if ((t & 63) == 0 && present) emask[i >> 6] = bal;   // lane 0 holds a multiple of 64
+  count_lds(cnt_s, cChiRange, nrange);
+  count_lds(cnt_s, cNanChi, nnan);
+  count_lds(cnt_s, cRetired, nret);
+  count_flush(cnt_s, a.counters);
+  // retired photons are dead too: the compaction of this species must not skip
+  if (t == 0 && a.killed && cnt_s[cRetired])
     atomicAdd((unsigned long long *)a.killed, (unsigned long long)cnt_s[cRetired]);
 }
 
@@ -2562,10 +2639,14 @@ hipError_t launch_pairs(qed_ctx *c, const qed_fields_t *f, const qed_species_t *
     const dim3 tgrid((unsigned)(ttiles < twgs ? ttiles : twgs));
     if (thin && a.ret.on)
       hipLaunchKernelGGL(k_photon_thin<true>, tgrid, dim3(kPTThreads), 0, st, a, c->cand_mask, clear);
+    else if (thin && f->kind == QED_FIELD_GRID)
+      hipLaunchKernelGGL(k_photon_grid<true>, dim3(gp_grid(ph->capacity, kGPThreads)), dim3(kGPThreads), 0, st, a,
+                         c->cand_mask, clear);
     else if (thin)
       hipLaunchKernelGGL(k_photon_thin<false>, tgrid, dim3(kPTThreads), 0, st, a, c->cand_mask, clear);
     else if (f->kind == QED_FIELD_GRID)
-      hipLaunchKernelGGL(k_photon_table<QED_FIELD_GRID>, tgrid, dim3(kPTThreads), 0, st, a, c->cand_mask, clear);
+      hipLaunchKernelGGL(k_photon_grid<false>, dim3(gp_grid(ph->capacity, kGPThreads)), dim3(kGPThreads), 0, st, a,
+                         c->cand_mask, clear);
     else if (f->kind == QED_FIELD_UNIFORM)
       hipLaunchKernelGGL(k_photon_table<QED_FIELD_UNIFORM>, tgrid, dim3(kPTThreads), 0, st, a, c->cand_mask, clear);
     else
