@@ -78,6 +78,35 @@ __device__ __forceinline__ R h_pair(R chi, const R *L, const TabRange &rg) {
   return M::ex(((R)1 - f) * L[i] + f * L[i + 1] - (R)8 * inv3chi);
 }
 
+// The same rates as their logarithms, which is what the tables hold: ln h where it
+// comes from the table, with `direct` set; otherwise h itself.  lnchi = ln chi.
+template <typename R>
+__device__ __forceinline__ R ln_h_rad(R chi, R lnchi, const R *lnh, const TabRange &rg, bool &direct) {
+  direct = chi >= (R)kRadChiMin && chi <= (R)rg.rad_hi;
+  if (!direct) return h_rad<R>(chi, lnh, rg);
+  const R x = (lnchi - (R)rg.rad_lnlo) * (R)rg.rad_inv;
+  int i = (int)floor(x);
+  i = i < 0 ? 0 : (i > kRadNChi - 2 ? kRadNChi - 2 : i);
+  const R f = x - (R)i;
+  return ((R)1 - f) * lnh[i] + f * lnh[i + 1];
+}
+// (float32: below exp(-87), where h loses digits and then vanishes, h as well)
+template <typename R>
+__device__ __forceinline__ R ln_h_pair(R chi, R lnchi, const R *L, const TabRange &rg, bool &direct) {
+  direct = chi >= (R)kPairChiMin && chi <= (R)rg.pair_hi;
+  if (!direct) return h_pair<R>(chi, L, rg);
+  const R x = (lnchi - (R)rg.pair_lnlo) * (R)rg.pair_rate_inv;
+  int i = (int)floor(x);
+  i = i < 0 ? 0 : (i > kPairNRate - 2 ? kPairNRate - 2 : i);
+  const R f = x - (R)i;
+  const R l = ((R)1 - f) * L[i] + f * L[i + 1] - (R)8 / ((R)3 * chi);
+  if constexpr (sizeof(R) == 4) {
+    direct = l >= -87.f;
+    if (!direct) return exp(l);
+  }
+  return l;
+}
+
 // Envelopes of the total rates for Poisson thinning (the surrogate path):
 // closed forms that lie above the rates everywhere, so that candidate events
 // drawn at the envelope rate and kept with probability h / h_env are exactly

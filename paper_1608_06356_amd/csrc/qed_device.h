@@ -50,23 +50,32 @@ constexpr int kCounterSlots = 64;              // copies of the counters (see co
 // ------------------------------------------------------------------ Philox
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): 10 rounds of two 32x32->64
 // multiplications with the round keys advanced by the Weyl constants.
+// Wide: one 32 x 32 -> 64 bit multiplication each (18 of the 36 quarter-rate
+// instructions, a few registers more: for kernels that have them to spare).
+template <bool Wide = false>
 __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint2 k) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     if (r) { k.x += 0x9E3779B9u; k.y += 0xBB67AE85u; }
-    const uint32_t lo0 = 0xD2511F53u * c.x, hi0 = __umulhi(0xD2511F53u, c.x);
-    const uint32_t lo1 = 0xCD9E8D57u * c.z, hi1 = __umulhi(0xCD9E8D57u, c.z);
-    c = make_uint4(hi1 ^ c.y ^ k.x, lo1, hi0 ^ c.w ^ k.y, lo0);
+    if constexpr (Wide) {
+      const uint64_t m0 = (uint64_t)0xD2511F53u * c.x, m1 = (uint64_t)0xCD9E8D57u * c.z;
+      c = make_uint4((uint32_t)(m1 >> 32) ^ c.y ^ k.x, (uint32_t)m1, (uint32_t)(m0 >> 32) ^ c.w ^ k.y, (uint32_t)m0);
+    } else {
+      const uint32_t lo0 = 0xD2511F53u * c.x, hi0 = __umulhi(0xD2511F53u, c.x);
+      const uint32_t lo1 = 0xCD9E8D57u * c.z, hi1 = __umulhi(0xCD9E8D57u, c.z);
+      c = make_uint4(hi1 ^ c.y ^ k.x, lo1, hi0 ^ c.w ^ k.y, lo0);
+    }
   }
   return c;
 }
 
+template <bool Wide = false>
 __device__ __forceinline__ uint4 stream4(uint64_t id, uint32_t seed, uint64_t step,
                                          uint32_t purpose, uint32_t k) {
   const uint2 key = make_uint2((uint32_t)id, (uint32_t)(id >> 32) ^ seed);
   const uint4 ctr = make_uint4((uint32_t)step,
                                ((uint32_t)(step >> 32) & 0x00FFFFFFu) | (purpose << 24), k, 0u);
-  return philox4x32_10(ctr, key);
+  return philox4x32_10<Wide>(ctr, key);
 }
 
 // u = ((x >> 9) + 0.5) 2^-23: exact in float and double, never 0 or 1.
@@ -116,6 +125,9 @@ __device__ __forceinline__ double ln_any(double x) {
   return x > 0.0 ? (x < INFINITY ? r : x) : (x == 0.0 ? -INFINITY : NAN);
 }
 __device__ __forceinline__ float ln_any(float x) { return logf(x); }
+
+// ln kRateUnit
+__device__ __forceinline__ double log_rate_unit() { return 8.0088952168030988626; }
 
 // Optical depth of a draw.
 __device__ __forceinline__ double draw_tau(uint32_t u) { return -ln_finite(unit<double>(u)); }

@@ -2266,7 +2266,7 @@ __global__ void k_init_tau(const uint64_t *id, double *tau, const int64_t *count
   const uint64_t step = step_of(step_v, d_step);
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n && i < cap;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const uint4 u = stream4(id[i], seed, step, kInitTau, 0u);
+    const uint4 u = stream4<true>(id[i], seed, step, kInitTau, 0u);
     tau[i] = draw_tau(u.x);
   }
 }
@@ -2320,42 +2320,125 @@ __global__ void k_eval_chi(SpeciesDev sp, FieldDev f, int photon, double *out) {
   }
 }
 
+// ------------------------------------------------------- standalone sampler
+// Two neighbouring quantiles of a row, in one read.
+__device__ __forceinline__ void quantile_pair(const RowF64 &t, int row, int j, double &a, double &b) {
+  struct Two { double a, b; } v;
+  __builtin_memcpy(&v, t.S + row * kNU + j, sizeof(v));
+  a = v.a; b = v.b;
+}
+struct RowQ16Pair {
+  const uint16_t *q;
+  const float2 *s0sc;      // offset and scale of a row
+  __device__ __forceinline__ float at(int row, int j) const { return s0sc[row].x + (float)q[row * kNU + j] * s0sc[row].y; }
+};
+__device__ __forceinline__ void quantile_pair(const RowQ16Pair &t, int row, int j, float &a, float &b) {
+  uint32_t v;
+  __builtin_memcpy(&v, t.q + row * kNU + j, sizeof(v));
+  const float2 o = t.s0sc[row];
+  a = o.x + (float)(v & 0xFFFFu) * o.y;
+  b = o.x + (float)(v >> 16) * o.y;
+}
+
+// 1 / (1 + exp(-s)) for |s| < 87.  float32: exp2 of the hardware at s log2(e) in two
+// parts and its reciprocal refined once, each within two units in the last place.
+__device__ __forceinline__ double sigmoid(double s) { return 1.0 / (1.0 + exp(-s)); }
+__device__ __forceinline__ float sigmoid(float s) {
+  const float p = -s * 1.44269502f, e = fmaf(-s, 1.44269502f, -p) - s * 1.92596303e-8f;
+  const float r = __builtin_amdgcn_exp2f(p), d = 1.f + fmaf(r * 0.69314718f, e, r);
+  const float y = __builtin_amdgcn_rcpf(d);
+  return fmaf(fmaf(-d, y, 1.f), y, y);
+}
+// logit u of a draw (1 - u is exact)
+__device__ __forceinline__ double logit_draw(double u) { return ln_finite(u) - ln_finite(1.0 - u); }
+__device__ __forceinline__ float logit_draw(float u) {
+  return 0.69314718f * (__builtin_amdgcn_logf(u) - __builtin_amdgcn_logf(1.f - u));
+}
+
+// ln W_rad, one xi and ln W_pair: sample_rad, h_rad and h_pair with what the three
+// share evaluated once (ln chi, ln gamma; ln h is read, not taken of an exponential).
 template <typename R, typename Tab>
-__device__ void sample_one(const Tab &tab, const R *lnh, const R *L, double chi, double gamma,
-                           uint64_t id, uint32_t seed, uint64_t step, float *lnw, float *xi_out,
-                           float *lnwp, int64_t i, const TabRange &rg) {
-  const R h = h_rad<R>((R)chi, lnh, rg);
-  lnw[i] = (float)log(kRateUnit * (double)h / gamma);
-  const uint4 u = stream4(id, seed, step, kLeptonEvent, 0u);
-  R xi, om;
-  sample_rad<R>(tab, (R)chi, unit<R>(u.x), unit<R>(u.z), xi, om, rg);
+__device__ __forceinline__ void sample_one(const Tab &tab, const R *lnh, const R *L, double chi_d, double gamma,
+                                           uint64_t id, uint32_t seed, uint64_t step, float *lnw, float *xi_out,
+                                           float *lnwp, int64_t i, const TabRange &rg) {
+  const R chi = (R)chi_d, lnchi = ln_any(chi);
+  // ln of W = kRateUnit h / gamma from ln h, or from h
+  const double lng = log_rate_unit() - ln_any(gamma);
+  auto ln_rate = [&](R h, bool direct) {
+    double r = (double)h + lng;
+    if (!direct) r = h == (R)0 && gamma > 0.0 ? -INFINITY : ln_any(kRateUnit * (double)h / gamma);
+    return (float)r;
+  };
+  bool direct;
+  R h = ln_h_rad<R>(chi, lnchi, lnh, rg, direct);
+  lnw[i] = ln_rate(h, direct);
+  const uint4 u = stream4<true>(id, seed, step, kLeptonEvent, 0u);
+  const int row = pick_row<R>(lnchi, unit<R>(u.z), rg.rad_lnlo, rg.rad_inv);
+  const R uu = unit<R>(u.x), y = (logit_draw(uu) - (R)rg.rad_tlo) * (R)rg.rad_tinv;
+  R xi;
+  if (y >= (R)0) {
+    int j = (int)floor(y);
+    j = j > kNU - 2 ? kNU - 2 : j;
+    const R f = y >= (R)(kNU - 1) ? (R)1 : y - (R)j;
+    R a, b;
+    quantile_pair(tab, row, j, a, b);
+    xi = sigmoid(((R)1 - f) * a + f * b);
+  } else {
+    const R r = uu / (R)kRadULo;
+    xi = sigmoid((R)tab.at(row, 0)) * r * r * r;
+  }
+  if (chi < (R)kRadChiMin) xi = xi * (chi / (R)kRadChiMin);
   xi_out[i] = (float)xi;
   if (lnwp) {
-    const R hp = gamma >= 2.0 ? h_pair<R>((R)chi, L, rg) : (R)0;
-    lnwp[i] = (float)log(kRateUnit * (double)hp / gamma);
+    direct = false;
+    h = (R)0;
+    if (gamma >= 2.0) h = ln_h_pair<R>(chi, lnchi, L, rg, direct);
+    lnwp[i] = ln_rate(h, direct);
   }
 }
 
-__global__ void k_sample_f64(const double *chi, const double *gamma, const uint64_t *id, int64_t n,
-                             const double *lnh, const double *L, const double *S64, uint32_t seed,
-                             uint64_t step_v, const int64_t *d_step, float *lnw, float *xi, float *lnwp,
-                             TabRange rg) {
+// Stay: a workgroup stages the rate tables and the rows' offsets in LDS and takes many
+// samples; otherwise they are read through the caches.  What bounds a large call: per
+// sample the instructions of Philox (quarter-rate multiplications) and of two
+// logarithms, and the scattered read of a quantile pair; its 36 bytes of input and
+// output take 0.36 ms per 5e7.  5e7 samples, float32 0.78 -> 0.51 ms, float64 1.28 ->
+// 0.70 (before: ln W from an exponential and a logarithm, six scattered reads).
+template <bool Stay>
+__global__ __launch_bounds__(256) void k_sample_f64(const double *chi, const double *gamma, const uint64_t *id, int64_t n,
+                                                    const double *lnh, const double *L, const double *S64, uint32_t seed,
+                                                    uint64_t step_v, const int64_t *d_step, float *lnw, float *xi,
+                                                    float *lnwp, TabRange rg) {
+  __shared__ double lnh_s[Stay ? kRadNChi : 1], L_s[Stay ? kPairNRate : 1];
+  if constexpr (Stay) {
+    for (int k = threadIdx.x; k < kRadNChi; k += 256) lnh_s[k] = lnh[k];
+    for (int k = threadIdx.x; k < kPairNRate; k += 256) L_s[k] = L[k];
+    __syncthreads();
+  }
   const uint64_t step = step_of(step_v, d_step);
   const RowF64 tab{S64};
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    sample_one<double>(tab, lnh, L, chi[i], gamma[i], id[i], seed, step, lnw, xi, lnwp, i, rg);
+  for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+    sample_one<double>(tab, Stay ? lnh_s : lnh, Stay ? L_s : L, chi[i], gamma[i], id[i], seed, step, lnw, xi, lnwp, i,
+                       rg);
 }
 
-__global__ void k_sample_f32(const double *chi, const double *gamma, const uint64_t *id, int64_t n,
-                             const float *lnh, const float *L, const uint16_t *q16, const float *s0sc,
-                             uint32_t seed, uint64_t step_v, const int64_t *d_step, float *lnw, float *xi,
-                             float *lnwp, TabRange rg) {
+template <bool Stay>
+__global__ __launch_bounds__(256) void k_sample_f32(const double *chi, const double *gamma, const uint64_t *id, int64_t n,
+                                                    const float *lnh, const float *L, const uint16_t *q16,
+                                                    const float *s0sc, uint32_t seed, uint64_t step_v,
+                                                    const int64_t *d_step, float *lnw, float *xi, float *lnwp,
+                                                    TabRange rg) {
+  __shared__ float lnh_s[Stay ? kRadNChi : 1], L_s[Stay ? kPairNRate : 1];
+  __shared__ float2 s0sc_s[Stay ? kRadNChi : 1];
+  const float2 *rows = reinterpret_cast<const float2 *>(s0sc);
+  if constexpr (Stay) {
+    for (int k = threadIdx.x; k < kRadNChi; k += 256) { lnh_s[k] = lnh[k]; s0sc_s[k] = rows[k]; }
+    for (int k = threadIdx.x; k < kPairNRate; k += 256) L_s[k] = L[k];
+    __syncthreads();
+  }
   const uint64_t step = step_of(step_v, d_step);
-  const RowQ16 tab{q16, s0sc};
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    sample_one<float>(tab, lnh, L, chi[i], gamma[i], id[i], seed, step, lnw, xi, lnwp, i, rg);
+  const RowQ16Pair tab{q16, Stay ? s0sc_s : rows};
+  for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+    sample_one<float>(tab, Stay ? lnh_s : lnh, Stay ? L_s : L, chi[i], gamma[i], id[i], seed, step, lnw, xi, lnwp, i, rg);
 }
 
 }  // namespace qed
@@ -2790,18 +2873,22 @@ hipError_t launch_eval_chi(qed_ctx *c, const qed_fields_t *f, const qed_species_
 hipError_t launch_sample(qed_ctx *c, const double *chi, const double *gamma, const uint64_t *id,
                          int64_t n, int precision, int64_t step, float *lnw, float *xi, float *lnwp,
                          hipStream_t st) {
-  int64_t blocks = (n + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  if (blocks < 1) blocks = 1;
-  if (precision == QED_F64)
-    hipLaunchKernelGGL(k_sample_f64, dim3((unsigned)blocks), dim3(256), 0, st, chi, gamma, id, n,
-                       c->rad_lnh64, c->pair_L64, c->rad_S64, c->params.seed, (uint64_t)step,
-                       step < 0 ? c->d_step : nullptr, lnw,
-                       xi, lnwp, c->range);
-  else
-    hipLaunchKernelGGL(k_sample_f32, dim3((unsigned)blocks), dim3(256), 0, st, chi, gamma, id, n,
-                       c->rad_lnh32, c->pair_L32, c->rad_q16, c->rad_s0sc, c->params.seed,
-                       (uint64_t)step, step < 0 ? c->d_step : nullptr, lnw, xi, lnwp, c->range);
+  // Staging costs a load and a barrier per workgroup: 8.3 -> 8.9 us a call of 1e3 or
+  // 3e5, against the reads it saves from a full chip on: 5e6 float32 55 -> 47 us.
+  const bool stay = n >= (int64_t)1 << 20;
+  const int64_t all = (n + 255) / 256, kept = 16 * (int64_t)c->n_cu;
+  const dim3 grid((unsigned)(stay && all > kept ? kept : (all < 65536 ? all : 65536)));
+  const int64_t *dstep = step < 0 ? c->d_step : nullptr;
+  const uint32_t seed = c->params.seed;
+  if (precision == QED_F64) {
+    auto k = stay ? k_sample_f64<true> : k_sample_f64<false>;
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, st, chi, gamma, id, n, c->rad_lnh64, c->pair_L64, c->rad_S64, seed,
+                       (uint64_t)step, dstep, lnw, xi, lnwp, c->range);
+  } else {
+    auto k = stay ? k_sample_f32<true> : k_sample_f32<false>;
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, st, chi, gamma, id, n, c->rad_lnh32, c->pair_L32, c->rad_q16,
+                       c->rad_s0sc, seed, (uint64_t)step, dstep, lnw, xi, lnwp, c->range);
+  }
   return hipGetLastError();
 }
 

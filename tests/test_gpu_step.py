@@ -933,3 +933,54 @@ def test_box_staging_equals_global_gather():
     gb = np.sort(np.linalg.norm(b["ph_k"], axis=1))
     if ga.size == gb.size:
         np.testing.assert_allclose(gb, ga, rtol=1e-5)
+
+
+@pytest.mark.parametrize("n", [1, 255, 257, (1 << 20) - 1, 1 << 20, (1 << 20) + 77])
+def test_sample_edges(rad_table_I, pair_table, n):
+    """Both kernels of the sampler over chi and gamma of every branch: zero, below
+    and above the tables, where float32 loses h_pair, gamma below 2.  ln W is float32
+    of a sum of terms up to 300 whose tables are float32 (2e-5 relative in W and four
+    units in the last place of ln W); where h_pair is subnormal in float32, one unit
+    of it more (half below one unit either way: -inf)."""
+    torch, q = need_gpu()
+    ctx = q.Context(seed=6)
+    ctx.qed_build_tables(q.QED_FORMULA_I)
+    edge = np.array([0.0, 1e-30, 1e-6, 9.99e-4, 1e-3, 0.00999, 0.01, 0.011, 0.02, 0.0255, 0.026, 0.03, 0.0306, 0.031,
+                     1.0, 99.9, 100.0, 101.0, 1e6])
+    chi = np.resize(edge, n)
+    gam = np.resize(np.array([1.0, 1.999, 2.0, 2.5, 1e3, 1e7, 1e-3]), n)
+    ids = np.arange(n, dtype=np.uint64) * np.uint64(0x9E3779B97F4A7C15)
+    dev = lambda a, dt: torch.from_numpy(a).to("cuda", dt)
+    tchi, tg = dev(chi, torch.float64), dev(gam, torch.float64)
+    tid = dev(ids.view(np.int64), torch.int64)
+    from oracle import philox
+    u = philox.uniform(philox.stream(ids, 6, 3, philox.LEPTON_EVENT, 0))
+    rad, pair = mc.RadSampler(rad_table_I, "f64"), mc.PairSampler(pair_table, "f64")
+    with np.errstate(divide="ignore"):
+        lw, lwp = np.log(rad.rate(chi, gam)), np.log(pair.rate(chi, gam))
+    h = pair.rate(chi, np.full(n, 2.0)) * 2.0 / RATE_UNIT
+    # float32 rounds the mixing fraction of a row by up to 1e-5: not the draws beside it
+    with np.errstate(divide="ignore"):
+        pos = np.log(np.maximum(chi, tables.RAD_CHI_MIN) / tables.RAD_CHI_MIN) / np.log(100.0 / tables.RAD_CHI_MIN) * 255
+    beside = np.abs((pos - u[:, 2] + 0.5) % 1.0 - 0.5) < 1e-4
+    for prec, storage, tol_s in ((q.QED_F64, "f64", 1e-10), (q.QED_F32, "q16", 3e-3)):
+        print(f"sample: n={n} precision {prec}", flush=True)
+        lnw = torch.empty(n, dtype=torch.float32, device="cuda")
+        xi, lnwp = torch.empty_like(lnw), torch.empty_like(lnw)
+        ctx.qed_sample(tchi, tg, tid, prec, 3, lnw, xi, lnwp)
+        got = [v.cpu().numpy().astype(np.float64) for v in (lnw, xi, lnwp)]
+        near = lambda a, b, more: np.all((a == b) | (np.abs(a - b) <= 2e-5 + 4 * 2.0 ** -23 * np.abs(b) + more))
+        with np.errstate(invalid="ignore"):
+            assert near(got[0], lw, 0.0)
+            if prec == q.QED_F64:
+                ok = np.ones(n, bool)
+                assert near(got[2], lwp, 0.0)
+            else:
+                unit32 = 2.0 ** -149
+                ok = h > 4 * unit32
+                assert near(got[2][ok], lwp[ok], unit32 / np.maximum(h[ok], 2.0 ** -126) + 2 * unit32 / h[ok])
+                assert np.all(np.isneginf(got[2][h < 0.25 * unit32]))
+        xr, _ = mc.RadSampler(rad_table_I, storage).sample(chi, u[:, 0], u[:, 2])
+        far = np.abs(got[1] - xr) > tol_s * xr * (1 - xr) + 4e-7 * xr + 2.0 ** -149
+        assert not np.any(far & ~beside)
+    ctx.close()
