@@ -161,12 +161,17 @@ __device__ __forceinline__ void gather_grid(const FieldDev &f, R x, R y, R z, R 
 // vector L1 returns per particle from 27 x 24 to about the box's share.  A
 // workgroup whose box exceeds its capacity gathers from global memory.
 // 4 T nodes for T threads: the LDS allows 24 waves per CU whatever T.
+// A node is 16 + 8 bytes in two arrays: LDS gives a wave's 16-byte reads at about 215
+// bytes a cycle and its 8-byte reads at 145 (measured, without conflicts), and three
+// 8-byte reads per node kept it busy for 3/4 of the lepton pass.  Lepton pass of 6e7
+// electrons on 96^3, 68 per cell: 1.23 -> 1.15 ms; 1e7 on 128^3: 0.344 -> 0.325.
 constexpr int kGPWaves = 6;
 
 template <int T>
 struct BoxLds {
   static constexpr int kCap = 4 * T;
-  float2 node[kCap * 3];        // 6 floats per node; node (x, y, z) at z * pxy + y * px + x
+  float4 lo4[kCap];             // floats 0..3 of node (x, y, z) at z * pxy + y * px + x
+  float2 hi2[kCap];             // floats 4 and 5
   int ref[3];                   // centre node of the workgroup's first particle
   int lo[3], hi[3];             // extremes of the centre nodes relative to ref
   int bad;                      // a particle's stencil left the box (then: global gather)
@@ -262,7 +267,6 @@ __device__ __forceinline__ bool stage_box(BoxLds<T> &S, const FieldDev &f, const
   }
   // box coordinates are below 2^11 and pitches below 2^11 (24-bit products);
   // the grid plane stride in floats may exceed 2^24 (full 32-bit product)
-  unsigned char *lds = reinterpret_cast<unsigned char *>(S.node);
   if (inside) {
     const uint32_t sy6 = (uint32_t)f.nx * 6u, sz6 = (uint32_t)f.nx * (uint32_t)f.ny * 6u;
     const float *gb = f.grid + (uint32_t)g0[2] * sz6 + (uint32_t)g0[1] * sy6 + (uint32_t)g0[0] * 6u;
@@ -275,8 +279,8 @@ __device__ __forceinline__ bool stage_box(BoxLds<T> &S, const FieldDev &f, const
       const float2 *g2 = reinterpret_cast<const float2 *>(gb + go);
       const float2 v0 = g2[0], v1 = g2[1], v2 = g2[2];
       const uint32_t a = __umul24(z, (uint32_t)pxy) + __umul24(y, (uint32_t)px) + x;
-      float2 *d = reinterpret_cast<float2 *>(lds + __umul24(a, 24u));
-      d[0] = v0; d[1] = v1; d[2] = v2;
+      S.lo4[a] = make_float4(v0.x, v0.y, v1.x, v1.y);
+      S.hi2[a] = v2;
     }
   } else {
     for (int p = threadIdx.x; p < cnt; p += T) {
@@ -290,8 +294,8 @@ __device__ __forceinline__ bool stage_box(BoxLds<T> &S, const FieldDev &f, const
       const float2 *g2 = reinterpret_cast<const float2 *>(f.grid + ((gz * (uint32_t)f.ny + gy) * (uint32_t)f.nx + gx) * 6u);
       const float2 v0 = g2[0], v1 = g2[1], v2 = g2[2];
       const uint32_t a = __umul24((uint32_t)z, (uint32_t)pxy) + __umul24((uint32_t)y, (uint32_t)px) + (uint32_t)x;
-      float2 *d = reinterpret_cast<float2 *>(lds + __umul24(a, 24u));
-      d[0] = v0; d[1] = v1; d[2] = v2;
+      S.lo4[a] = make_float4(v0.x, v0.y, v1.x, v1.y);
+      S.hi2[a] = v2;
     }
   }
   // the stencil of every live particle lies inside the box by construction;
@@ -314,9 +318,7 @@ __device__ __forceinline__ bool stage_box(BoxLds<T> &S, const FieldDev &f, const
   return S.bad == 0;
 }
 
-// Gather from the staged box.  A row of the stencil (three nodes along x) is
-// 72 contiguous bytes of LDS; row offsets are byte offsets built from the
-// pitches with adds only.  DB: the next row's reads are issued before the
+// Gather from the staged box, a row of the stencil (three nodes along x) at a time.  DB: the next row's reads are issued before the
 // current row's products, so that LDS latency overlaps the arithmetic (18 more
 // registers); without it the other waves of the SIMD hide that latency.
 template <typename R, bool DB = true, int T>
@@ -324,31 +326,34 @@ __device__ __forceinline__ void gather_box(const BoxLds<T> &S, const int c0[3], 
                                            R F[6]) {
 #pragma unroll
   for (int c = 0; c < 6; ++c) F[c] = (R)0;
-  const uint32_t pb0 = (uint32_t)pit[0] * 24u, pb1 = (uint32_t)pit[1] * 24u;   // uniform
-  const uint32_t b0 = (uint32_t)__umul24((uint32_t)c0[2], pb1) + (uint32_t)__umul24((uint32_t)c0[1], pb0) +
-                      (uint32_t)c0[0] * 24u;
-  const unsigned char *lds = reinterpret_cast<const unsigned char *>(S.node);
-  float2 v[2][9];
-  auto load_row = [&](float2 *dst, int r) {
-    const float2 *q = reinterpret_cast<const float2 *>(lds + b0 + (uint32_t)(r / 3) * pb1 + (uint32_t)(r % 3) * pb0);
+  const uint32_t px = (uint32_t)pit[0], pxy = (uint32_t)pit[1];   // uniform
+  const uint32_t n0 = (uint32_t)__umul24((uint32_t)c0[2], pxy) + (uint32_t)__umul24((uint32_t)c0[1], px) +
+                      (uint32_t)c0[0];
+  const float4 *const b4 = S.lo4 + n0;
+  const float2 *const b2 = S.hi2 + n0;
+  float4 v4[2][3];
+  float2 v2[2][3];
+  auto load_row = [&](int buf, int r) {
+    const uint32_t o = (uint32_t)(r / 3) * pxy + (uint32_t)(r % 3) * px;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) dst[k] = q[k];
+    for (int k = 0; k < 3; ++k) { v4[buf][k] = b4[o + k]; v2[buf][k] = b2[o + k]; }
   };
-  if constexpr (DB) load_row(v[0], 0);
+  if constexpr (DB) load_row(0, 0);
 #pragma unroll
   for (int r = 0; r < 9; ++r) {
     if constexpr (DB) {
-      if (r + 1 < 9) load_row(v[(r + 1) & 1], r + 1);
+      if (r + 1 < 9) load_row((r + 1) & 1, r + 1);
     } else {
-      load_row(v[r & 1], r);
+      load_row(r & 1, r);
     }
-    const float2 *u = v[r & 1];
     const R wyz = w[1][r % 3] * w[2][r / 3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       const R wt = w[0][a] * wyz;
-      F[0] += wt * (R)u[3 * a].x; F[1] += wt * (R)u[3 * a].y; F[2] += wt * (R)u[3 * a + 1].x;
-      F[3] += wt * (R)u[3 * a + 1].y; F[4] += wt * (R)u[3 * a + 2].x; F[5] += wt * (R)u[3 * a + 2].y;
+      const float4 u = v4[r & 1][a];
+      const float2 t = v2[r & 1][a];
+      F[0] += wt * (R)u.x; F[1] += wt * (R)u.y; F[2] += wt * (R)u.z;
+      F[3] += wt * (R)u.w; F[4] += wt * (R)t.x; F[5] += wt * (R)t.y;
     }
   }
 }
