@@ -2051,7 +2051,8 @@ __global__ __launch_bounds__(kGPThreads, 5) void k_photon_grid(PairArgs<float> a
   }
   if (!Thin)
     for (int k = t; k < kPairNRate; k += T) L_s[k] = a.L[k];
-  const float gph = root<float>(kx * kx + ky * ky + kz * kz);
+  // (rounded as the pass without a box rounds it, so that both leave the same positions)
+  const float gph = root<float>(fmaf(kz, kz, fmaf(kx, kx, ky * ky)));
   if (a.move && alive && gph > 0.f) {
     const float vdt = rcp<float>(gph) * a.dt;
     x += kx * vdt; y += ky * vdt; z += kz * vdt;
