@@ -184,3 +184,29 @@ def test_photon_pass_on_a_grid_staged_equals_global(n, surrogate):
     assert a[3:] == b[3:] and (n < 1000 or a[3] > 0)
     for u, v in zip(a[:3], b[:3]):
         assert np.array_equal(u, v)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("n", [0, 1, 3, 4, 1023, 1024, 1029, 8193])
+def test_sort_moves_every_array(dtype, n):
+    """All arrays of a species go through one permutation at the ends of its groups of
+    four and of its blocks; the values are moved, so they are equal bit for bit."""
+    torch, q = need_gpu()
+    rng = np.random.default_rng(n + 1)
+    ng, L = 12, 2 * math.pi
+    x = rng.uniform(0, L, (n, 3)).astype(np.float32).astype(np.float64)
+    p = rng.normal(size=(n, 3)).astype(np.float32).astype(np.float64)
+    tau, ids = rng.uniform(size=n), rng.permutation(n).astype(np.uint64) + np.uint64(7)
+    ctx = q.Context()
+    a, b = q.Species(n + 5, dtype), q.Species(n + 9, dtype)
+    a.load(x, p, tau, ids)
+    grid = torch.zeros(ng ** 3 * 6, dtype=torch.float32, device="cuda")
+    print(f"sort: {dtype} n={n}", flush=True)
+    ctx.qed_sort_by_cell(q.Fields(q.QED_FIELD_GRID, grid=grid, n=ng, L=L), a, b)
+    got = b.to_numpy()
+    assert b.n() == n
+    back = np.argsort(got["id"])
+    order = np.argsort(ids)
+    for k, want in (("id", ids), ("x", x), ("p", p), ("tau", tau)):
+        assert np.array_equal(got[k][back], want[order])
+    ctx.close()
