@@ -423,7 +423,11 @@ struct InferLds {
   float chk[kRadNChi * (2 + 2 * kChkN)];
 };
 
-constexpr int kInferThreads = 512;
+// Bound by the instructions of the activations (48 exponentials and reciprocals a lane
+// per net and tile).  Three waves per SIMD: 1e7 samples 1.96 (two) -> 1.76 ms; four
+// spill (1.77), two tiles per read of the weights gain less (1.81).  A small call spreads
+// its waves over all workgroups: 1e3 samples 34 -> 26 us, 5e5 114 -> 92.
+constexpr int kInferThreads = 768;
 
 __global__ __launch_bounds__(kInferThreads) void k_infer(InferArgs a) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -437,7 +441,8 @@ __global__ __launch_bounds__(kInferThreads) void k_infer(InferArgs a) {
   const int64_t ntile = (a.n + 63) / 64;     // 64 samples per wave, one per lane
   const int wpb = blockDim.x >> 6;
   uint32_t nfx = 0, nfr = 0;
-  for (int64_t tile = (int64_t)blockIdx.x * wpb + (threadIdx.x >> 6); tile < ntile;
+  // (wave-major, so that few tiles spread over all the workgroups)
+  for (int64_t tile = (int64_t)(threadIdx.x >> 6) * gridDim.x + blockIdx.x; tile < ntile;
        tile += (int64_t)gridDim.x * wpb) {
     reload_barrier();
     const int64_t i = tile * 64 + lane;
@@ -445,7 +450,7 @@ __global__ __launch_bounds__(kInferThreads) void k_infer(InferArgs a) {
     const double chi = valid ? a.chi[i] : 1.0;
     const double gam = valid ? a.gamma[i] : 1.0;
     const uint64_t id = valid ? a.id[i] : 0;
-    const uint4 r = stream4(id, a.seed, a.d_step ? (uint64_t)*a.d_step : a.step, kLeptonEvent, 0u);
+    const uint4 r = stream4<true>(id, a.seed, a.d_step ? (uint64_t)*a.d_step : a.step, kLeptonEvent, 0u);
     const float u = unit<float>(r.x), urow = unit<float>(r.z);
     const float t = logf(u) - log1pf(-u);
     const bool in_chi = chi >= kRadChiMin && chi <= kRadChiMax;
@@ -496,9 +501,10 @@ __global__ __launch_bounds__(kInferThreads) void k_infer(InferArgs a) {
       sample_rad<float>(tab, (float)chi, u, urow, xi, om, a.rg);
     }
     if (valid) {
-      a.lnw[i] = (float)((double)lh + log(kRateUnit / gam));
+      const double lng = log_rate_unit() - ln_any(gam);   // ln W = ln h + lng
+      a.lnw[i] = (float)((double)lh + lng);
       a.xi[i] = xi;
-      if (a.lnwp) a.lnwp[i] = isfinite(lhp) ? (float)((double)lhp + log(kRateUnit / gam)) : -INFINITY;
+      if (a.lnwp) a.lnwp[i] = isfinite(lhp) ? (float)((double)lhp + lng) : -INFINITY;
       nfx += !xi_ok;
       nfr += !rate_ok;
     }
@@ -600,7 +606,7 @@ hipError_t launch_mlp_sample(qed_ctx *c, const double *chi, const double *gamma,
               step < 0 ? c->d_step : nullptr,
               c->rad_lnh32, c->pair_L32, c->rad_s0sc, c->rad_chk, c->rad_q16, lnw, xi, lnwp, tol,
               c->d_counters + cMlpFallbackXi, make_range(kRadChiMax, kPairChiMax)};
-  int64_t blocks = ((n + 63) / 64 + 7) / 8;
+  int64_t blocks = (n + 63) / 64;
   if (blocks > c->n_cu) blocks = c->n_cu;      // one workgroup per CU (LDS-bound)
   if (blocks < 1) blocks = 1;
   hipLaunchKernelGGL(k_infer, dim3((unsigned)blocks), dim3(kInferThreads), sizeof(InferLds), st, a);

@@ -193,7 +193,10 @@ __device__ __forceinline__ void forward_inf(const NetLdsI &s, int nin, int nout,
   }
 }
 
-__device__ __forceinline__ float xin(double chi) { return (float)((log10(chi) + kXShift) / kXScale); }
+// chi > 0, finite
+__device__ __forceinline__ float xin(double chi) {
+  return (float)((ln_finite(chi) * 0.43429448190325182765 + kXShift) / kXScale);
+}
 
 // ------------------------------------------------------------ residual check
 // Photon CDF of the table row r on 40 nodes uniform in s over the row's fine
