@@ -106,7 +106,7 @@ int ensure_emitters(qed_ctx *c, int64_t n) {
   if (e != hipSuccess) return hip_fail(c, e, "reserve");
   free_emitters(c);
   if ((e = dalloc(&c->em_idx, n)) != hipSuccess || (e = dalloc(&c->em_rec, kEmRecMaxBytes * n)) != hipSuccess ||
-      (e = dalloc(&c->em_mask, n / 64 + 1)) != hipSuccess || (e = dalloc(&c->cont_idx, n)) != hipSuccess ||
+      (e = dalloc(&c->em_mask, 3 * (n / 64 + 1))) != hipSuccess || (e = dalloc(&c->cont_idx, n)) != hipSuccess ||
       (e = dalloc(&c->d_n_cont, 1)) != hipSuccess) {
     free_emitters(c);
     return hip_fail(c, e, "reserve: hipMalloc");

@@ -194,8 +194,9 @@ __device__ __forceinline__ void forward_inf(const NetLdsI &s, int nin, int nout,
 }
 
 // chi > 0, finite
+template <bool Near = false>
 __device__ __forceinline__ float xin(double chi) {
-  return (float)((ln_finite(chi) * 0.43429448190325182765 + kXShift) / kXScale);
+  return (float)((ln_finite<Near>(chi) * 0.43429448190325182765 + kXShift) / kXScale);
 }
 
 // ------------------------------------------------------------ residual check

@@ -90,6 +90,15 @@ template <typename R> __device__ __forceinline__ R unit(uint32_t x) {
 // leading digits, so the error is below one unit in the last place.  About 40
 // instructions where the library's function, which works in pairs of float64,
 // takes 130: the event kernels are bound by the latency of such chains.
+// Near: the coefficients are moved into registers where they are used.  The compiler
+// otherwise keeps them in 20 vector registers across the loop around the call, which
+// a kernel with no register to spare pays for with spills.
+template <bool Near>
+__device__ __forceinline__ double coefficient(double c) {
+  if constexpr (Near) asm volatile("" : "+s"(c));
+  return c;
+}
+template <bool Near = false>
 __device__ __forceinline__ double ln_finite(double x) {
   double m = __builtin_amdgcn_frexp_mant(x);              // [1/2, 1)
   int k = __builtin_amdgcn_frexp_exp(x);
@@ -103,16 +112,16 @@ __device__ __forceinline__ double ln_finite(double x) {
   double s = f * y;
   s = fma(fma(-d, s, f), y, s);
   const double z = s * s, h = 0.5 * f * f;
-  double r = 2.0 / 21.0;
-  r = fma(r, z, 2.0 / 19.0);
-  r = fma(r, z, 2.0 / 17.0);
-  r = fma(r, z, 2.0 / 15.0);
-  r = fma(r, z, 2.0 / 13.0);
-  r = fma(r, z, 2.0 / 11.0);
-  r = fma(r, z, 2.0 / 9.0);
-  r = fma(r, z, 2.0 / 7.0);
-  r = fma(r, z, 2.0 / 5.0);
-  r = fma(r, z, 2.0 / 3.0);
+  double r = coefficient<Near>(2.0 / 21.0);
+  r = fma(r, z, coefficient<Near>(2.0 / 19.0));
+  r = fma(r, z, coefficient<Near>(2.0 / 17.0));
+  r = fma(r, z, coefficient<Near>(2.0 / 15.0));
+  r = fma(r, z, coefficient<Near>(2.0 / 13.0));
+  r = fma(r, z, coefficient<Near>(2.0 / 11.0));
+  r = fma(r, z, coefficient<Near>(2.0 / 9.0));
+  r = fma(r, z, coefficient<Near>(2.0 / 7.0));
+  r = fma(r, z, coefficient<Near>(2.0 / 5.0));
+  r = fma(r, z, coefficient<Near>(2.0 / 3.0));
   // k ln 2 in two parts, the first exact for |k| < 2^11
   constexpr double kLn2Hi = 0x1.62e42fefa38p-1, kLn2Lo = 0x1.ef35793c7673p-45;
   const double kd = (double)k, t = kd * kLn2Hi, sum = t + f, e = f - (sum - t);   // t + f = sum + e
@@ -120,8 +129,9 @@ __device__ __forceinline__ double ln_finite(double x) {
 }
 
 // The same with the logarithm's values at zero, infinity, below zero and for NaN.
+template <bool Near = false>
 __device__ __forceinline__ double ln_any(double x) {
-  const double r = ln_finite(x);
+  const double r = ln_finite<Near>(x);
   return x > 0.0 ? (x < INFINITY ? r : x) : (x == 0.0 ? -INFINITY : NAN);
 }
 __device__ __forceinline__ float ln_any(float x) { return logf(x); }
@@ -130,7 +140,8 @@ __device__ __forceinline__ float ln_any(float x) { return logf(x); }
 __device__ __forceinline__ double log_rate_unit() { return 8.0088952168030988626; }
 
 // Optical depth of a draw.
-__device__ __forceinline__ double draw_tau(uint32_t u) { return -ln_finite(unit<double>(u)); }
+template <bool Near = false>
+__device__ __forceinline__ double draw_tau(uint32_t u) { return -ln_finite<Near>(unit<double>(u)); }
 
 // ---------------------------------------------------------------- chi
 // Eq. (2) rearranged without subtraction of nearly equal squares: with n = p/|p|,

@@ -519,8 +519,9 @@ __device__ __forceinline__ bool retirable(const RetireDev &r, double tau, float 
 }
 
 // bin = floor((ln gamma - ln 2) / d) with d = (ln 1e7 - ln 2) / kTallyBins, clamped
+template <bool Near = false>
 __device__ __forceinline__ void tally_photon(const RetireDev &r, double gph) {
-  const double b = floor((log(gph) - kTallyLnLo) * (kTallyBins / (kTallyLnHi - kTallyLnLo)));
+  const double b = floor((ln_any<Near>(gph) - kTallyLnLo) * (kTallyBins / (kTallyLnHi - kTallyLnLo)));
   const int k = b < 0.0 ? 0 : (b >= (double)kTallyBins ? kTallyBins - 1 : (int)b);
   atomicAdd(&r.tally[k], 1ull);
 }
@@ -932,7 +933,7 @@ struct EmitArgs {
   const uint16_t *q16;         // 16-bit quantiles (R = float)
   const float *s0sc;
   const EmIdx *em_idx;
-  const EmRec<R> *rec;
+  EmRec<R> *rec;
   const int64_t *n_emit;
   uint64_t *next_id;
   uint32_t seed;
@@ -1250,10 +1251,10 @@ __device__ __forceinline__ float mlp_packed(const mlp::NetLdsI &N, int nin, int 
 
 // ln h_rad(chi) from net B for the lanes of a wave with `need`; ok = inside the
 // trained chi range, finite and below the thinning envelope (else the caller
-// takes the table).
-__device__ __forceinline__ float mlp_lnh(const mlp::NetLdsI &B, double chi, bool need, bool &ok) {
+// takes the table).  x0 = mlp::xin(chi), or of 1 outside the range.
+__device__ __forceinline__ float mlp_lnh(const mlp::NetLdsI &B, double chi, float x0, bool need, bool &ok) {
   const bool in = chi >= kRadChiMin && chi <= kMlpChiMax;
-  const float mine = mlp_packed<0>(B, 1, 1, need, mlp::xin(in ? chi : 1.0), 0.f);   // the photon rate head only
+  const float mine = mlp_packed<0>(B, 1, 1, need, x0, 0.f);   // the photon rate head only
   const float lchi = logf((float)chi);
   const float lh = mlp::kBShift0 + mlp::kBScale0 * mine + lchi;
   ok = need && in && isfinite(lh) && expf(lh) <= h_rad_env((float)chi);
@@ -1271,7 +1272,86 @@ __device__ __forceinline__ float mlp_lnh_pair(const mlp::NetLdsI &B, double chi,
   return lh;
 }
 
-constexpr int kEmitMlpThreads = 512;
+template <bool Cont>
+constexpr int emit_mlp_threads() { return Cont ? 512 : 768; }
+
+// A photon to be stored, at its emitter's position in the list, and the masks over the
+// list of the emitters with an accepted photon and of those with one to be stored.
+struct EmPhoton {
+  float gph, n[3], x[3];
+  double tau;
+};
+static_assert(sizeof(EmRec<float>) + sizeof(EmPhoton) <= kEmRecMaxBytes, "both fit a record slot");
+struct EmPhotons {
+  uint64_t *acc, *keep;
+  EmPhoton *at;
+};
+
+constexpr int kEATile = kEIThreads * 64;
+
+// Appends the photons of the first surrogate pass in emitter order (ids and slots as
+// in append_photons): a thread scans one mask word, then a wave takes its 64 words one
+// by one, an emitter per lane.
+__global__ __launch_bounds__(kEIThreads) void k_emit_append(SpeciesDev ph, const int64_t *n_emit, EmPhotons p,
+                                                            uint64_t *next_id, ScanDev sc,
+                                                            unsigned long long *counters) {
+  __shared__ uint64_t scan_s[16];
+  __shared__ uint64_t off_s;
+  __shared__ uint16_t list_s[kEIThreads / 64][64 * 64];
+  __shared__ uint32_t tile_s, cnt_s[cNumCounters];
+  __shared__ int64_t hdr_s[2];
+  const int64_t n_em = *n_emit, ntiles = (n_em + kEATile - 1) / kEATile;
+  if (idle_block(ntiles)) return;
+  count_zero(cnt_s);
+  if (threadIdx.x == 0) { hdr_s[0] = *ph.count; hdr_s[1] = (int64_t)*next_id; }
+  const int lane = threadIdx.x & 63;
+  float *X = (float *)ph.x, *Y = (float *)ph.y, *Z = (float *)ph.z;
+  float *KX = (float *)ph.px, *KY = (float *)ph.py, *KZ = (float *)ph.pz;
+  uint32_t ndrop = 0;
+  while (true) {
+    const uint32_t tile = next_tile(sc.ticket, &tile_s);   // its barriers also publish the header
+    if ((int64_t)tile >= ntiles) break;
+    const int64_t ph0 = hdr_s[0], w0 = (int64_t)tile * kEIThreads + (threadIdx.x & ~63), w = w0 + lane;
+    const uint64_t id0 = (uint64_t)hdr_s[1];
+    const uint64_t acc = w * 64 < n_em ? p.acc[w] : 0, keep = w * 64 < n_em ? p.keep[w] : 0;
+    uint64_t tot;
+    const uint64_t off = block_exclusive64((uint64_t)__popcll(acc) | ((uint64_t)__popcll(keep) << 31), scan_s, &tot);
+    const uint64_t toff = tile_offset(tile, tot, sc.status, counters, &off_s);
+    const uint64_t base = toff + off;
+    // the wave's photons as a list of (word, bit), so that its lanes load them at once
+    uint16_t *list = list_s[threadIdx.x >> 6];
+    const uint64_t first = __shfl(base, 0, 64) >> 31;
+    uint32_t q = (uint32_t)((base >> 31) - first);
+    for (uint64_t k = keep; k; k &= k - 1) list[q++] = (uint16_t)((lane << 6) | (__ffsll((unsigned long long)k) - 1));
+    const uint32_t m = __shfl(q, 63, 64);
+    __syncthreads();
+    for (uint32_t c = 0; c < m; c += 64) {
+      const bool mine = c + lane < m;
+      const uint32_t e = mine ? list[c + lane] : 0u, bit = e & 63u;
+      const uint64_t a = __shfl(acc, e >> 6, 64), b = __shfl(base, e >> 6, 64);
+      if (!mine) continue;
+      const int64_t j = ph0 + (int64_t)(first + c + lane);
+      if (j < ph.cap) {
+        const EmPhoton v = p.at[(w0 + (e >> 6)) * 64 + bit];
+        X[j] = v.x[0]; Y[j] = v.x[1]; Z[j] = v.x[2];
+        KX[j] = v.n[0] * v.gph; KY[j] = v.n[1] * v.gph; KZ[j] = v.n[2] * v.gph;
+        ph.tau[j] = v.tau;
+        ph.id[j] = id0 + (b & 0x7FFFFFFFull) + (uint64_t)__popcll(a & ((1ull << bit) - 1ull));
+      } else {
+        ++ndrop;
+      }
+    }
+    if ((int64_t)tile == ntiles - 1 && threadIdx.x == 0) {
+      const uint64_t t = toff + tot;
+      const int64_t n = ph0 + (int64_t)(t >> 31);
+      *ph.count = n < ph.cap ? n : ph.cap;
+      *next_id = id0 + (t & 0x7FFFFFFFull);
+    }
+    if (single_turn(ntiles)) break;
+  }
+  count_lds(cnt_s, cDropped, ndrop);
+  count_flush(cnt_s, counters);
+}
 
 struct EmitMlpLds {
   mlp::NetLdsI A, B;
@@ -1291,18 +1371,27 @@ struct EmitMlpLds {
 //
 // Two passes.  Cont = false takes every emitter's first candidate; with
 // kmax > 1 an emitter with a further candidate within the step sets its bit in
-// cont_mask (at its position in the emitter list) and is left to the second
-// pass.  Cont = true takes the emitters of that list (cont_idx, n_cont, in
-// emitter order), re-runs their first candidate (identical: the same streams
-// and per-lane arithmetic; neither counted nor appended again) and goes on with
-// candidates 1 .. kmax - 1.  Packed densely, the few emitters with a second
-// candidate fill whole net calls instead of a few lanes of every wave.  The
-// photons of the second pass follow all those of the first, in (emitter, event)
-// order.
+// cont_mask (at its position in the emitter list), leaves its state in its record
+// and is left to the second pass.  Cont = true takes the emitters of that list
+// (cont_idx, n_cont, in emitter order) with candidates 1 .. kmax - 1.  Packed
+// densely, the few emitters with a second candidate fill whole net calls instead of a
+// few lanes of every wave.  The photons of the second pass follow all those of the
+// first, in (emitter, event) order.
+//
+// The first pass appends nothing: its photons (one per emitter at most, nearly all of
+// them retired in the cascades) are put down beside their records and k_emit_append
+// stores them, so its waves take 64 emitters at a time in any order and wait neither
+// for each other nor for earlier tiles.  With the append in this kernel, a tile of 512
+// waited for the slowest of the 255 others.  What bounds it: float64 and activation
+// instructions (half of the time), the scattered record, id and momentum (1.2 GB a
+// launch of 2e6 emitters).  Three waves per SIMD.  Launches of 2.1e6 emitters on
+// average: 513 -> 384 us and 9 of k_emit_append; two waves 408.  The second pass:
+// SECOND.
 template <bool Cont>
-__global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a, MlpDev m, uint64_t *cont_mask,
+__global__ __launch_bounds__((emit_mlp_threads<Cont>())) void k_emit_mlp(EmitArgs<float> a, MlpDev m, uint64_t *cont_mask,
                                                               const int32_t *cont_idx, const int64_t *n_cont,
-                                                              ScanClear clear) {
+                                                              EmPhotons out, ScanClear clear) {
+  constexpr int kThreads = emit_mlp_threads<Cont>();
   extern __shared__ __align__(16) unsigned char lds_raw[];
   EmitMlpLds &S = *reinterpret_cast<EmitMlpLds *>(lds_raw);
   __shared__ uint64_t scan_s[16];
@@ -1320,7 +1409,7 @@ __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a,
   __syncthreads();
   const int64_t n_em = hdr_s[0], ph0 = hdr_s[1];
   const uint64_t id0 = (uint64_t)hdr_s[2];
-  const int64_t ntiles = (n_em + kEmitMlpThreads - 1) / kEmitMlpThreads;
+  const int64_t ntiles = (n_em + (Cont ? kThreads : 64) - 1) / (Cont ? kThreads : 64);
   if (idle_block(ntiles)) return;
   const int klim = Cont ? a.kmax : 1;
   mlp::stage_net_infer(m.thA, mlp::kA, &S.A);
@@ -1329,69 +1418,91 @@ __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a,
   for (int k = threadIdx.x; k < kRadNChi; k += blockDim.x) S.lnh[k] = m.lnh32[k];
   const RowQ16 tab{m.q16, m.s0sc};     // fallback: 16-bit table through the caches
   const uint64_t step = step_of(a.step, a.d_step);
-  while (true) {
-    const uint32_t tile = next_tile(a.sc.ticket, &tile_s);
-    if ((int64_t)tile >= ntiles) break;
-    const int64_t r = (int64_t)tile * kEmitMlpThreads + threadIdx.x;
+  constexpr int kSlots = Cont ? kKmaxMax : 1;
+  if (!Cont) __syncthreads();
+  // Cont: tiles of the workgroup in ticket order; else a wave's 64 emitters, no order
+  int64_t tile = blockIdx.x + (int64_t)gridDim.x * (threadIdx.x >> 6);
+  for (;; tile += (int64_t)gridDim.x * (kThreads / 64)) {
+    if (Cont) tile = next_tile(a.sc.ticket, &tile_s);
+    if (tile >= ntiles) break;
+    const int64_t r = Cont ? tile * kThreads + threadIdx.x : tile * 64 + (threadIdx.x & 63);
     const bool valid = r < n_em;
-    float gph[kKmaxMax];
-    double tph[kKmaxMax];
+    float gph[kSlots];
+    double tph[kSlots];
     uint32_t nacc = 0, nev = 0, nrej = 0, ncap = 0, nfx = 0, nfr = 0, nnull = 0, nexc = 0;
     float nx = 0, ny = 0, nz = 0, x = 0, y = 0, z = 0, px = 0, py = 0, pz = 0, g = 1;
     float F[6] = {0, 0, 0, 0, 0, 0};
-    double chi = 1.0, Wenv = 0.0, rem = 0.0, tau = 0.0, sq = kEnvSqueeze;
+    double chi = 1.0, Wenv = 0.0, rem = 0.0, tau = 0.0;
+    float looser = 1.f;        // of the squeeze
     uint64_t id = 0;
     int64_t i = 0;
+    int32_t slot = 0;
     bool recoiled = false;
     if (valid) {
       const EmIdx e = a.em_idx[Cont ? (int64_t)cont_idx[r] : r];
       i = e.i;
       id = a.lep.id[i];
-      const EmRec<float> rc = a.rec[e.slot];
+      slot = e.slot;
+      const EmRec<float> rc = a.rec[slot];
 #pragma unroll
       for (int c = 0; c < 6; ++c) F[c] = rc.F[c];
-      // chi itself, in float64; the lepton pass ran the envelope at its bound
-      // rc.chi >= chi, so the squeeze (a lower bound of W / W_env) scales by
-      // h_env(chi) / h_env(rc.chi) <= 1
-      chi = chi_lepton_f32(rc.p[0], rc.p[1], rc.p[2], rc.F);
-      const float he = h_rad_env((float)rc.chi);
-      sq = he > 0.f ? kEnvSqueeze * (double)(h_rad_env((float)chi) / he) : 0.0;
-      Wenv = rc.W; rem = a.dtd - rc.tau / rc.W;   // time left after the first candidate
-      px = rc.p[0]; py = rc.p[1]; pz = rc.p[2];
       x = rc.x[0]; y = rc.x[1]; z = rc.x[2];
-      const float pa = sqrtf(px * px + py * py + pz * pz);
-      if (pa > 0.f) { nx = px / pa; ny = py / pa; nz = pz / pa; }
-      g = sqrtf(1.f + px * px + py * py + pz * pz);
+      Wenv = rc.W;
+      if constexpr (Cont) {
+        // as the first pass left it: direction, gamma (negative: after a recoil)
+        nx = rc.p[0]; ny = rc.p[1]; nz = rc.p[2];
+        const float sg = __int_as_float(rc.j0);
+        recoiled = sg < 0.f;
+        g = fabsf(sg);
+        looser = __int_as_float(rc.nsub);
+        chi = rc.chi;
+        rem = rc.tau;
+        const float pm = sqrtf(fmaxf(g * g - 1.f, 0.f));
+        px = nx * pm; py = ny * pm; pz = nz * pm;
+      } else {
+        // chi itself, in float64; the lepton pass ran the envelope at its bound
+        // rc.chi >= chi, so the squeeze (a lower bound of W / W_env) scales by
+        // h_env(chi) / h_env(rc.chi) <= 1
+        chi = chi_lepton_f32(rc.p[0], rc.p[1], rc.p[2], rc.F);
+        const float he = h_rad_env((float)rc.chi);
+        looser = he > 0.f ? h_rad_env((float)chi) / he : 0.f;
+        rem = a.dtd - rc.tau / rc.W;   // time left after the first candidate
+        px = rc.p[0]; py = rc.p[1]; pz = rc.p[2];
+        const float pa = sqrtf(px * px + py * py + pz * pz);
+        if (pa > 0.f) { nx = px / pa; ny = py / pa; nz = pz / pa; }
+        g = sqrtf(1.f + px * px + py * py + pz * pz);
+      }
     }
     bool active = valid;       // a candidate is pending at time dt - rem
-    for (int k = 0; k < klim; ++k) {
+    for (int k = Cont ? 1 : 0; k < klim; ++k) {
       if (!__any(active)) break;
       mlp::reload_barrier();
-      const bool counted = !Cont || k > 0;   // the second pass re-runs candidate 0 silently
       // keep the candidate with probability W / W_env: below the squeeze the
       // draw keeps it at once, above it W comes from net B (packed over the
       // lanes that need it)
       const double ukeep = unit<double>(stream4(id, a.seed, step, kLeptonThin, (uint32_t)k).x);
+      const double sq = kEnvSqueeze * (double)looser;
       const bool need_w = active && !(ukeep < sq);
       bool ok;
-      const float lh = mlp_lnh(S.B, chi, need_w, ok);
+      const bool in_chi = chi >= kRadChiMin && chi <= kMlpChiMax;
+      const float xa0 = mlp::xin<true>(in_chi ? chi : 1.0);
+      const float lh = mlp_lnh(S.B, chi, xa0, need_w, ok);
       bool keep = active && ukeep < sq;
       if (need_w) {
         float h = 0.f;
         if (isfinite(chi) && chi > 0.0) {
           h = ok ? expf(lh) : h_rad<float>((float)chi, S.lnh, m.rg);
-          nfr += counted && !ok;
+          nfr += !ok;
         }
         const double W = kRateUnit * (double)(h / g);
-        nexc += counted && (W > Wenv || W < sq * Wenv);
+        nexc += W > Wenv || W < sq * Wenv;
         keep = ukeep * Wenv < W;
       }
-      nnull += counted && active && !keep;
+      nnull += active && !keep;
       const uint4 u = stream4(id, a.seed, step, kLeptonEvent, (uint32_t)k);
       const float uxi = unit<float>(u.x), urow = unit<float>(u.z);
       const float t = logf(uxi) - log1pf(-uxi);
-      const bool in_chi = chi >= kRadChiMin && chi <= kMlpChiMax;
-      const float xa0 = mlp::xin(in_chi ? chi : 1.0), xa1 = t / (float)mlp::kTmax;
+      const float xa1 = t / (float)mlp::kTmax;
       const float yA = mlp_packed<0>(S.A, 2, 1, keep, xa0, xa1);   // only the kept candidates
       if (keep) {
         const float lchi = logf((float)chi);
@@ -1412,17 +1523,15 @@ __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a,
         } else {
           sample_rad<float>(tab, (float)chi, uxi, urow, xi, om, m.rg);
         }
-        nev += counted;
-        nfx += counted && !xi_ok;
+        ++nev;
+        nfx += !xi_ok;
         const float gp = xi * g;
         if (gp >= 2.f) {
-          if (counted) {
-            const double tp = draw_tau(u.w);
+          const double tp = draw_tau<true>(u.w);
 #pragma unroll
-            for (int sl = 0; sl < kKmaxMax; ++sl)
-              if (sl == (int)nacc) { gph[sl] = gp; tph[sl] = tp; }
-            ++nacc;
-          }
+          for (int sl = 0; sl < kSlots; ++sl)
+            if (sl == (int)nacc) { gph[sl] = gp; tph[sl] = tp; }
+          ++nacc;
           if (a.recoil) {
             const float gn = fmaxf(om * g, 1.f);
             const float pm = sqrtf(fmaxf(gn * gn - 1.f, 0.f));
@@ -1431,14 +1540,14 @@ __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a,
             recoiled = true;
             chi = chi_lepton(px, py, pz, F[0], F[1], F[2], F[3], F[4], F[5]);
             Wenv = isfinite(chi) ? kRateUnit * (double)(h_rad_env((float)chi) / g) : 0.0;
-            sq = kEnvSqueeze;
+            looser = 1.f;
           }
         } else {
-          nrej += counted;
+          ++nrej;
         }
       }
       if (active) {
-        tau = draw_tau(u.y);
+        tau = draw_tau<true>(u.y);
         const bool again = Wenv > 0.0 && tau <= Wenv * rem;
         if (!again) {
           active = false;
@@ -1453,9 +1562,24 @@ __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a,
     // first pass: a lane still active has a further candidate within the step
     const bool cont = !Cont && active;
     if (!Cont) {
-      const uint64_t cb = __ballot(cont);
-      const int64_t r0 = (int64_t)tile * kEmitMlpThreads + (threadIdx.x & ~63);
-      if ((threadIdx.x & 63) == 0 && r0 < n_em) cont_mask[r0 >> 6] = cb;
+      bool kept = nacc > 0;
+      if (kept && retirable(a.ret, tph[0], gph[0], time_left(a.ret, step, a.dtd))) {
+        tally_photon<true>(a.ret, (double)gph[0]);
+        kept = false;
+      }
+      if (kept) out.at[r] = EmPhoton{gph[0], {nx, ny, nz}, {x, y, z}, tph[0]};
+      if (cont) {
+        EmRec<float> &w = a.rec[slot];
+        w.p[0] = nx; w.p[1] = ny; w.p[2] = nz;
+        w.j0 = __float_as_int(recoiled ? -g : g);
+        w.nsub = __float_as_int(looser);
+        w.chi = chi;
+        w.tau = rem;
+        w.W = Wenv;
+      }
+      const uint64_t cb = __ballot(cont), ab = __ballot(nacc > 0), kb = __ballot(kept);
+      if ((threadIdx.x & 63) == 0) { cont_mask[tile] = cb; out.acc[tile] = ab; out.keep[tile] = kb; }
+      count_lds(cnt_s, cRetired, nacc > 0 && !kept);
     }
     if (valid && !cont) {
       a.lep.tau[i] = tau - Wenv * rem;
@@ -1469,9 +1593,11 @@ __global__ __launch_bounds__(kEmitMlpThreads) void k_emit_mlp(EmitArgs<float> a,
     count_lds(cnt_s, cMlpFallbackRate, nfr);
     count_lds(cnt_s, cThinned, nnull);
     count_lds(cnt_s, cEnvelopeExceeded, nexc);
-    append_photons<float>(a.ph, a.ret, step, a.dtd, tile, n_em, kEmitMlpThreads, nacc, gph, tph, x, y, z, nx, ny, nz,
-                          ph0, id0, a.next_id, a.sc, a.counters, scan_s, &off_s, cnt_s);
-    if (single_turn(ntiles)) break;
+    if constexpr (Cont) {
+      append_photons<float>(a.ph, a.ret, step, a.dtd, (uint32_t)tile, n_em, kThreads, nacc, gph, tph, x, y, z, nx,
+                            ny, nz, ph0, id0, a.next_id, a.sc, a.counters, scan_s, &off_s, cnt_s);
+      if (single_turn(ntiles)) break;
+    }
   }
   count_flush(cnt_s, a.counters);
 }
@@ -2610,7 +2736,7 @@ template <typename R>
 static EmitArgs<R> emit_args(qed_ctx *c, const qed_species_t *lep, const qed_species_t *ph, int64_t step, int recoil,
                              const ScanDev &sc) {
   return EmitArgs<R>{dev_species(lep), dev_species(ph), rad_lnh<R>(c), c->rad_S64, c->rad_q16, c->rad_s0sc,
-                     c->em_idx, (const EmRec<R> *)c->em_rec, c->d_n_emit, c->d_next_id, c->params.seed,
+                     c->em_idx, (EmRec<R> *)c->em_rec, c->d_n_emit, c->d_next_id, c->params.seed,
                      c->params.kmax, recoil, (uint64_t)step, step < 0 ? c->d_step : nullptr, sc, c->d_counters,
                      gen_mode(c), c->em_dt, c->range, retire_dev(c)};
 }
@@ -2643,7 +2769,7 @@ hipError_t launch_emit(qed_ctx *c, const qed_species_t *lep, const qed_species_t
   const int64_t eit = wide ? ei_tile<8>() : ei_tile<1>();
   const int64_t etiles = (lep->capacity + eit - 1) / eit;
   const unsigned eig = (unsigned)(etiles < 2 * (int64_t)c->n_cu ? etiles : 2 * (int64_t)c->n_cu);   // persistent
-  const int tile = use_mlp ? kEmitMlpThreads
+  const int tile = use_mlp ? emit_mlp_threads<true>()
                            : (lep->dtype == QED_F32 ? (m1 ? emit_threads<float, true>() : emit_threads<float, false>())
                                                     : (m1 ? emit_threads<double, true>() : emit_threads<double, false>()));
   const int64_t ntiles = (lep->capacity + tile - 1) / tile;
@@ -2662,10 +2788,18 @@ hipError_t launch_emit(qed_ctx *c, const qed_species_t *lep, const qed_species_t
   const unsigned grid = (unsigned)(ntiles < wgs ? ntiles : wgs);
   if (use_mlp) {
     EmitArgs<float> a = emit_args<float>(c, lep, ph, step, recoil, sc);
+    // masks beside the emitter mask, photons behind the float32 records
+    const int64_t words = c->em_cap / 64 + 1;
+    const EmPhotons out{c->em_mask + words, c->em_mask + 2 * words,
+                        (EmPhoton *)(c->em_rec + c->em_cap * sizeof(EmRec<float>))};
     ScanClear clear{};
     if (c->params.kmax > 1 && (e = clear_region(c, clear, 0, kRegEmitIndex, etiles)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_emit_mlp<false>, dim3(grid), dim3(kEmitMlpThreads), sizeof(EmitMlpLds), st, a, mlp_dev(c),
-                       c->em_mask, (const int32_t *)nullptr, (const int64_t *)nullptr, clear);
+    hipLaunchKernelGGL(k_emit_mlp<false>, dim3(grid), dim3(emit_mlp_threads<false>()), sizeof(EmitMlpLds), st, a, mlp_dev(c),
+                       c->em_mask, (const int32_t *)nullptr, (const int64_t *)nullptr, out, clear);
+    const int64_t atiles = (lep->capacity + kEATile - 1) / kEATile;
+    const unsigned ag = (unsigned)(atiles < 2 * (int64_t)c->n_cu ? atiles : 2 * (int64_t)c->n_cu);
+    hipLaunchKernelGGL(k_emit_append, dim3(ag), dim3(kEIThreads), 0, st, a.ph, c->d_n_emit, out, c->d_next_id, a.sc,
+                       c->d_counters);
     if (c->params.kmax > 1) {
       // the emitters with a further candidate (bits in the emitter mask, which
       // the list above no longer needs), listed in emitter order and finished
@@ -2677,8 +2811,8 @@ hipError_t launch_emit(qed_ctx *c, const qed_species_t *lep, const qed_species_t
         hipLaunchKernelGGL((k_emit_index<1, int32_t>), dim3(eig), dim3(kEIThreads), 0, st, c->em_mask, c->d_n_emit,
                            c->cont_idx, c->d_n_cont, isc, c->d_counters);
       a.sc = scan_region(c, kRegEmitCont);
-      hipLaunchKernelGGL(k_emit_mlp<true>, dim3(grid), dim3(kEmitMlpThreads), sizeof(EmitMlpLds), st, a,
-                         mlp_dev(c), (uint64_t *)nullptr, c->cont_idx, c->d_n_cont, ScanClear{});
+      hipLaunchKernelGGL(k_emit_mlp<true>, dim3(grid), dim3(emit_mlp_threads<true>()), sizeof(EmitMlpLds), st, a,
+                         mlp_dev(c), (uint64_t *)nullptr, c->cont_idx, c->d_n_cont, EmPhotons{}, ScanClear{});
     }
   } else if (lep->dtype == QED_F32) {
     const EmitArgs<float> a = emit_args<float>(c, lep, ph, step, recoil, sc);
