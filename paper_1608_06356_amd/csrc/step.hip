@@ -653,12 +653,13 @@ template <typename R, int FK, bool M1> constexpr int gp_waves() {
   return (sizeof(R) == 4 && FK == QED_FIELD_GRID && !M1) ? kGPWaves : 1;
 }
 
-// First particle of this workgroup's tile, for tiles of `tile_size` particles
-// dealt to the XCDs in chunks of kGPChunk tiles.
-__device__ __forceinline__ int64_t gp_tile_base(int64_t tile_size) {
-  const int64_t k = blockIdx.x / kXcds;
-  return (((k / kGPChunk) * kXcds + blockIdx.x % kXcds) * kGPChunk + k % kGPChunk) * tile_size;
+// First particle of this workgroup's tile (of block b's), for tiles of `tile_size`
+// particles dealt to the XCDs in chunks of kGPChunk tiles.
+__device__ __forceinline__ int64_t gp_tile_base(int64_t tile_size, int64_t b) {
+  const int64_t k = b / kXcds;
+  return (((k / kGPChunk) * kXcds + b % kXcds) * kGPChunk + k % kGPChunk) * tile_size;
 }
+__device__ __forceinline__ int64_t gp_tile_base(int64_t tile_size) { return gp_tile_base(tile_size, blockIdx.x); }
 
 template <typename R>
 struct GPTile {   // the tile's slices of the particle arrays (uniform bases, 32-bit offsets)
@@ -1726,7 +1727,7 @@ __device__ void pair_tile(const PairArgs<R> &a, const Tab &tab, const R *L, uint
       a.ph.tau[i] = tn;
       if (retirable(a.ret, tn, (float)gph, t_left)) {
         a.ph.id[i] = kDeadId;
-        tally_photon(a.ret, (double)gph);
+        tally_photon<true>(a.ret, (double)gph);
         ++nret;
       }
     }
@@ -1818,7 +1819,7 @@ __device__ __forceinline__ void photon_settle(const PairArgs<float> &a, int64_t 
   a.ph.tau[i] = tn;
   if (retirable(a.ret, tn, gph, t_left)) {
     a.ph.id[i] = kDeadId;
-    tally_photon(a.ret, (double)gph);
+    tally_photon<true>(a.ret, (double)gph);
     ++nret;
   }
 }
@@ -2148,70 +2149,82 @@ __global__ __launch_bounds__(kPTThreads, 4) void k_photon_table(PairArgs<float> 
 // registers and lose where boxes fall back).  Intervals of the table cascade: 3e6
 // electrons on 32^3 6.29 -> 4.61 ms, 1e7 on 64^3 18.9 -> 13.5, 5e6 on 128^3 16.5 ->
 // 13.6, 1e5 on 32^3 1.60 -> 1.33 (there one photon per thread counts, not four).
-template <bool Thin>
-__global__ __launch_bounds__(kGPThreads, 5) void k_photon_grid(PairArgs<float> a, uint64_t *emask, ScanClear clear) {
+// Loop: a workgroup takes every kPhotonGroups-th tile (whole rounds of the dealing).
+// Photon species are made for many more photons than they hold, and a workgroup for
+// each tile of the capacity took 2 ms to find 1.2e9 slots empty.  The loop needs four
+// waves per SIMD: the interval of 3e6 electrons takes 4.4 ms either way, of 1e7 on
+// 64^3 12.6 against 12.7, of 5e6 on 128^3 14.3 against 13.5; up to kPhotonGroups tiles
+// there is none (1e5 electrons: 1.23 ms, with it 1.27).
+constexpr int64_t kPhotonGroups = 16 * kXcds * kGPChunk;
+template <bool Thin, bool Loop>
+__global__ __launch_bounds__(kGPThreads, Loop ? 4 : 5) void k_photon_grid(PairArgs<float> a, uint64_t *emask, ScanClear clear) {
   constexpr int T = kGPThreads;
   __shared__ BoxLds<T> box_s;
   __shared__ float L_s[kPairNRate];
   __shared__ uint32_t cnt_s[cNumCounters];
   scan_clear(clear);
-  const int64_t n = *a.ph.count, base = gp_tile_base(T);
-  if (base >= n) return;
+  const int64_t n = *a.ph.count;
+  if (gp_tile_base(T) >= n) return;
   const int t = threadIdx.x;
-  const int64_t i = base + t;
   FieldDev f = a.f;
   f.kind = QED_FIELD_GRID;
-  const GPTile<float> P(a.ph, base);
   count_zero(cnt_s);
-  // present: in the species; alive: not converted (a converted photon not yet
-  // compacted away keeps its place, and its position, in the box)
-  const bool present = i < n;
-  bool alive = false;
-  float kx = 0.f, ky = 0.f, kz = 0.f, x = 0.f, y = 0.f, z = 0.f;
-  double tau = 0.0;
-  if (present) {
-    alive = a.ph.id[i] != kDeadId;
-    kx = P.px[t]; ky = P.py[t]; kz = P.pz[t];
-    x = P.x[t]; y = P.y[t]; z = P.z[t];
-    tau = P.tau[t];
-  }
   if (!Thin)
     for (int k = t; k < kPairNRate; k += T) L_s[k] = a.L[k];
-  // (rounded as the pass without a box rounds it, so that both leave the same positions)
-  const float gph = root<float>(fmaf(kz, kz, fmaf(kx, kx, ky * ky)));
-  if (a.move && alive && gph > 0.f) {
-    const float vdt = rcp<float>(gph) * a.dt;
-    x += kx * vdt; y += ky * vdt; z += kz * vdt;
-    wrap_coord<float>(x, box_len<float>(f, 0)); wrap_coord<float>(y, box_len<float>(f, 1));
-    wrap_coord<float>(z, box_len<float>(f, 2));
-    P.x[t] = x; P.y[t] = y; P.z[t] = z;
-  }
-  int j[1][3], rel[1][3], pit[2];
-  float w[3][3], F[6];
-  tsc_setup<float>(f, x, y, z, j[0], w);      // absent lanes hold x = 0: harmless, unused
-  if (stage_box<1, T>(box_s, f, &present, j, rel, pit)) {   // its barriers also publish L_s and cnt_s
-    if (alive) gather_box<float>(box_s, rel[0], pit, w, F);
-  } else {
-    if (alive) gather_global<float>(f, j[0], w, F);
-  }
   uint32_t nrange = 0, nnan = 0, nret = 0;
-  bool ev = false;
-  if (alive) {
-    double chi, W = 0.0;
-    if constexpr (Thin) {
-      chi = fields_finite<float>(F) ? chi_photon_f32(kx, ky, kz, F) : NAN;
-      if (isfinite(chi)) W = photon_envelope(a, chi, gph);
-    } else {
-      photon_rate_at<float>(a, L_s, F, kx, ky, kz, gph, chi, W);
+  for (int64_t b = blockIdx.x; ; b += gridDim.x) {
+    const int64_t base = gp_tile_base(T, b), i = base + t;
+    if (base >= n) break;
+    const GPTile<float> P(a.ph, base);
+    // present: in the species; alive: not converted (a converted photon not yet
+    // compacted away keeps its place, and its position, in the box)
+    const bool present = i < n;
+    bool alive = false;
+    float kx = 0.f, ky = 0.f, kz = 0.f, x = 0.f, y = 0.f, z = 0.f;
+    double tau = 0.0;
+    if (present) {
+      alive = a.ph.id[i] != kDeadId;
+      kx = P.px[t]; ky = P.py[t]; kz = P.pz[t];
+      x = P.x[t]; y = P.y[t]; z = P.z[t];
+      tau = P.tau[t];
     }
-    if (isfinite(chi)) nrange += chi > a.rg.pair_hi;
-    else ++nnan;
-    ev = W > 0.0 && tau <= W * a.dtd;
-    if (!ev)
-      photon_settle(a, i, tau - W * a.dtd, gph, time_left(a.ret, step_of(a.step, a.d_step), a.dtd), nret);
+    // (rounded as the pass without a box rounds it, so that both leave the same positions)
+    const float gph = root<float>(fmaf(kz, kz, fmaf(kx, kx, ky * ky)));
+    if (a.move && alive && gph > 0.f) {
+      const float vdt = rcp<float>(gph) * a.dt;
+      x += kx * vdt; y += ky * vdt; z += kz * vdt;
+      wrap_coord<float>(x, box_len<float>(f, 0)); wrap_coord<float>(y, box_len<float>(f, 1));
+      wrap_coord<float>(z, box_len<float>(f, 2));
+      P.x[t] = x; P.y[t] = y; P.z[t] = z;
+    }
+    int j[1][3], rel[1][3], pit[2];
+    float w[3][3], F[6];
+    tsc_setup<float>(f, x, y, z, j[0], w);      // absent lanes hold x = 0: harmless, unused
+    if (stage_box<1, T>(box_s, f, &present, j, rel, pit)) {   // its barriers also publish L_s and cnt_s
+      if (alive) gather_box<float>(box_s, rel[0], pit, w, F);
+    } else {
+      if (alive) gather_global<float>(f, j[0], w, F);
+    }
+    bool ev = false;
+    if (alive) {
+      double chi, W = 0.0;
+      if constexpr (Thin) {
+        chi = fields_finite<float>(F) ? chi_photon_f32(kx, ky, kz, F) : NAN;
+        if (isfinite(chi)) W = photon_envelope(a, chi, gph);
+      } else {
+        photon_rate_at<float>(a, L_s, F, kx, ky, kz, gph, chi, W);
+      }
+      if (isfinite(chi)) nrange += chi > a.rg.pair_hi;
+      else ++nnan;
+      ev = W > 0.0 && tau <= W * a.dtd;
+      if (!ev)
+        photon_settle(a, i, tau - W * a.dtd, gph, time_left(a.ret, step_of(a.step, a.d_step), a.dtd), nret);
+    }
+    const uint64_t bal = __ballot(ev);
+    if ((t & 63) == 0 && present) emask[i >> 6] = bal;   // lane 0 holds a multiple of 64
+    if constexpr (!Loop) break;
+    __syncthreads();   // the box is free
   }
-  const uint64_t bal = __ballot(ev);
-  if ((t & 63) == 0 && present) emask[i >> 6] = bal;   // lane 0 holds a multiple of 64
   count_lds(cnt_s, cChiRange, nrange);
   count_lds(cnt_s, cNanChi, nnan);
   count_lds(cnt_s, cRetired, nret);
@@ -2622,10 +2635,10 @@ static hipError_t clear_region(const qed_ctx *c, ScanClear &cl, int at, int k, i
 // Blocks of a gather/push launch for a species of this capacity, IT particles
 // per thread: every tile has its block (chunks per XCD, times the chunk, times
 // the 8 XCDs).
-static unsigned gp_grid(int64_t capacity, int64_t tile) {
+static int64_t gp_grid(int64_t capacity, int64_t tile) {
   const int64_t ntiles = (capacity + tile - 1) / tile;
   const int64_t cpx = ((ntiles + kGPChunk - 1) / kGPChunk + kXcds - 1) / kXcds;
-  return (unsigned)(cpx * kGPChunk * kXcds);
+  return cpx * kGPChunk * kXcds;
 }
 
 // Two particles per thread (k_gather_push2) for a dense float32 species on a grid.
@@ -2639,21 +2652,21 @@ static void launch_gp_kind_m(const GPArgs<R> &a, int kind, int64_t cap, bool den
   if (kind == QED_FIELD_GRID) {
     if constexpr (sizeof(R) == 4 && !M1) {
       if (dense) {
-        hipLaunchKernelGGL((k_gather_push2<Thin>), dim3(gp_grid(cap, 2 * kGPThreads)), dim3(kGPThreads), 0, st, a);
+        hipLaunchKernelGGL((k_gather_push2<Thin>), dim3((unsigned)gp_grid(cap, 2 * kGPThreads)), dim3(kGPThreads), 0, st, a);
         return;
       }
       if (cap >= kSparseMin && cap < kSparseGP * (int64_t)a.f.nx * a.f.ny * a.f.nz) {
-        hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_GRID, M1, Thin, 512>), dim3(gp_grid(cap, 512)), dim3(512), 0, st, a);
+        hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_GRID, M1, Thin, 512>), dim3((unsigned)gp_grid(cap, 512)), dim3(512), 0, st, a);
         return;
       }
     }
-    hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_GRID, M1, Thin>), dim3(gp_grid(cap, kGPThreads)), dim3(kGPThreads), 0, st,
+    hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_GRID, M1, Thin>), dim3((unsigned)gp_grid(cap, kGPThreads)), dim3(kGPThreads), 0, st,
                        a);
   } else if (kind == QED_FIELD_UNIFORM) {
-    hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_UNIFORM, M1, Thin>), dim3(gp_grid(cap, kGPThreads)), dim3(kGPThreads), 0,
+    hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_UNIFORM, M1, Thin>), dim3((unsigned)gp_grid(cap, kGPThreads)), dim3(kGPThreads), 0,
                        st, a);
   } else {
-    hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_PER_PARTICLE, M1, Thin>), dim3(gp_grid(cap, kGPThreads)),
+    hipLaunchKernelGGL((k_gather_push<R, QED_FIELD_PER_PARTICLE, M1, Thin>), dim3((unsigned)gp_grid(cap, kGPThreads)),
                        dim3(kGPThreads), 0, st, a);
   }
 }
@@ -2860,16 +2873,17 @@ hipError_t launch_pairs(qed_ctx *c, const qed_fields_t *f, const qed_species_t *
     if (ph->capacity > c->cand_cap) return hipErrorInvalidValue;
     const int64_t ttiles = (ph->capacity + kPTTile - 1) / kPTTile, twgs = (int64_t)c->n_cu * 8;
     const dim3 tgrid((unsigned)(ttiles < twgs ? ttiles : twgs));
+    const int64_t pgroups = gp_grid(ph->capacity, kGPThreads);
+    const bool loop = pgroups > kPhotonGroups;
+    auto pg = loop ? (thin ? k_photon_grid<true, true> : k_photon_grid<false, true>)
+                   : (thin ? k_photon_grid<true, false> : k_photon_grid<false, false>);
     if (thin && a.ret.on)
       hipLaunchKernelGGL(k_photon_thin<true>, tgrid, dim3(kPTThreads), 0, st, a, c->cand_mask, clear);
-    else if (thin && f->kind == QED_FIELD_GRID)
-      hipLaunchKernelGGL(k_photon_grid<true>, dim3(gp_grid(ph->capacity, kGPThreads)), dim3(kGPThreads), 0, st, a,
-                         c->cand_mask, clear);
+    else if (f->kind == QED_FIELD_GRID)
+      hipLaunchKernelGGL(pg, dim3((unsigned)(loop ? kPhotonGroups : pgroups)), dim3(kGPThreads), 0, st, a, c->cand_mask,
+                         clear);
     else if (thin)
       hipLaunchKernelGGL(k_photon_thin<false>, tgrid, dim3(kPTThreads), 0, st, a, c->cand_mask, clear);
-    else if (f->kind == QED_FIELD_GRID)
-      hipLaunchKernelGGL(k_photon_grid<false>, dim3(gp_grid(ph->capacity, kGPThreads)), dim3(kGPThreads), 0, st, a,
-                         c->cand_mask, clear);
     else if (f->kind == QED_FIELD_UNIFORM)
       hipLaunchKernelGGL(k_photon_table<QED_FIELD_UNIFORM>, tgrid, dim3(kPTThreads), 0, st, a, c->cand_mask, clear);
     else

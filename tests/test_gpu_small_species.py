@@ -210,3 +210,42 @@ def test_sort_moves_every_array(dtype, n):
     for k, want in (("id", ids), ("x", x), ("p", p), ("tau", tau)):
         assert np.array_equal(got[k][back], want[order])
     ctx.close()
+
+
+@pytest.mark.parametrize("surrogate", [False, True])
+def test_photon_pass_on_a_grid_in_rounds(surrogate):
+    """The same where a workgroup takes more than one tile: 4096 tiles of 256 and some
+    photons of the next round."""
+    test_photon_pass_on_a_grid_staged_equals_global(4096 * 256 + 300, surrogate)
+
+
+@pytest.mark.parametrize("n", [0, 1, 257, 70_001])
+def test_photon_pass_on_a_grid_either_side_of_the_rounds(n):
+    """A species whose capacity fills 4096 tiles and one with a tile more: equal ids and
+    pairs, positions bit for bit, optical depths to the rounding of a float32 rate
+    (two compilations: 64 units in the last place of W dt <= tau's scale of 1)."""
+    torch, q = need_gpu()
+    ng, L, dt = 32, workloads.BOX_L, 0.01
+    rng = np.random.default_rng(n + 2)
+    x = rng.uniform(0.0, L, (n, 3))
+    k = rng.normal(size=(n, 3))
+    k *= (10.0 ** rng.uniform(0.0, 4.0, n) / np.linalg.norm(k, axis=1))[:, None]
+    tau, ids = rng.exponential(size=n) * 0.05, np.arange(n, dtype=np.uint64)
+    out = []
+    for cap in (4096 * 256, 4096 * 256 + 1):
+        print(f"photon pass on a grid: n={n} capacity {cap}", flush=True)
+        ctx = q.Context(seed=3, kmax=4)
+        ctx.qed_build_tables(q.QED_FORMULA_I)
+        grid = torch.empty(ng ** 3 * 6, dtype=torch.float32, device="cuda")
+        fld = q.Fields(q.QED_FIELD_GRID, grid=grid, n=ng, L=L)
+        ctx.qed_fill_standing_wave(grid, ng, L, 1000.0, 0.3)
+        ph, el, po = q.Species(cap, "f32"), q.Species(n + 1, "f32"), q.Species(n + 1, "f32")
+        ph.load(x, k, tau, ids)
+        ctx.qed_set_next_id(n)
+        ctx.qed_create_pairs(fld, ph, el, po, dt, 0)
+        out.append((ph.to_numpy(), el.to_numpy(), ctx.qed_get_status()[0]))
+        ctx.close()
+    (pa, ea, sa), (pb, eb, sb) = out
+    assert sa == sb and (n < 1000 or sa["pairs"] > 0)
+    assert np.array_equal(pa["id"], pb["id"]) and np.array_equal(pa["x"], pb["x"]) and np.array_equal(ea["id"], eb["id"])
+    assert np.all(np.abs(pa["tau"] - pb["tau"]) <= ULPS["f32"] * np.maximum(1.0, np.abs(pa["tau"])))

@@ -321,6 +321,55 @@ def test_surrogate_emission_passes(trained):
     assert same.sum() == n - s1["capped"]     # the capped ones are those the second pass finishes
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 5000, 20000, 40000])
+def test_surrogate_appends(trained, n):
+    """The first pass's photons are ranked and stored by a kernel of its own.  With
+    retirement the photons stored are those of a run without it that are not counted
+    in the tally, with the same ids and values bit for bit and in the same order; with
+    a smaller capacity they are its first ones, the rest dropped.  Sizes around a
+    wave's 64 emitters and an append tile's 16384 (about three in five emit)."""
+    torch, q = need_gpu()
+    rng = np.random.default_rng(41 + n)
+    gam = np.where(rng.uniform(size=n) < 0.5, 206.0, 2060.0)
+    phi = rng.uniform(0.0, 2.0 * math.pi, n)
+    pm = np.sqrt(gam ** 2 - 1.0)
+    p = np.stack([pm * np.cos(phi), pm * np.sin(phi), np.zeros(n)], axis=-1)
+    tau0 = rng.exponential(size=n)
+
+    def run(cap, retire):
+        print(f"surrogate appends: n {n} capacity {cap} retirement {retire}", flush=True)
+        ctx = _with_weights(q, trained, seed=29, kmax=4, flags=q.QED_FLAG_SURROGATE)
+        if retire:
+            ctx.qed_set_retirement(0.22, 2e5)
+        lep, ph = q.Species(n, "f32"), q.Species(cap, "f32")
+        lep.load(np.zeros((n, 3)), p, tau=tau0, ids=np.arange(n, dtype=np.uint64))
+        ctx.qed_set_next_id(n)
+        ctx.qed_gather_push(q.Fields(q.QED_FIELD_UNIFORM, B=(0, 0, 2000.0)), lep, -1, 0.2, 0)
+        ctx.qed_emit_photons(lep, ph, 0)
+        st, _ = ctx.qed_get_status(check=False)
+        tally = int(ctx.qed_get_tally().sum()) if retire else 0
+        out = (lep.to_numpy(), ph.to_numpy(), st, tally)
+        ctx.close()
+        return out
+
+    la, pa, sa, _ = run(4 * n, False)
+    m = pa["id"].size
+    assert np.array_equal(pa["id"], n + np.arange(m, dtype=np.uint64)) and sa["photons"] == m
+    lb, pb, sb, tally = run(4 * n, True)
+    assert sb["photons"] == m and sb["retired"] == tally == m - pb["id"].size
+    assert n < 5000 or 0 < tally < m
+    at = (pb["id"] - np.uint64(n)).astype(np.int64)
+    assert np.all(np.diff(at) > 0)
+    for k in ("x", "p", "tau", "id"):
+        assert np.array_equal(la[k], lb[k])
+        assert np.array_equal(pb[k], pa[k][at])
+    cap = max(1, m // 3)
+    lc, pc, sc, _ = run(cap, False)
+    assert pc["id"].size == min(cap, m) and sc["dropped"] == m - min(cap, m)
+    for k in ("x", "p", "tau", "id"):
+        assert np.array_equal(pc[k], pa[k][:cap])
+
+
 def test_surrogate_step_spectrum_and_rate(trained):
     """The emission step with QED_FLAG_SURROGATE (candidate events at the rate
     envelope in the lepton pass, kept with the rate net's W / W_env, xi net in
