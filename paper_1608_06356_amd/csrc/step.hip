@@ -2257,7 +2257,7 @@ __global__ __launch_bounds__(256) void k_pair_events(PairArgs<float> a, const in
     const int64_t i = eidx[r];
     const uint64_t pid = a.ph.id[i];
     const float kx = KX[i], ky = KY[i], kz = KZ[i];
-    const float x = X[i], y = Y[i], z = Z[i];      // moved by k_photon_table
+    const float x = X[i], y = Y[i], z = Z[i];      // moved by the photon pass
     const float gph = root<float>(kx * kx + ky * ky + kz * kz);
     double chi, W;
     photon_rate<float>(a, L_s, i, x, y, z, kx, ky, kz, gph, chi, W);
