@@ -77,13 +77,16 @@ int ensure_scan(qed_ctx *c, int64_t n) {
   hipError_t e = hipDeviceSynchronize();
   if (e != hipSuccess) return hip_fail(c, e, "reserve");
   free_scan(c);
-  // particles per tile of each region's user; up to 2^18 particles the float64
-  // pair pass, and up to 2^17 the emission, takes tiles of 256
-  const int64_t tile[kScanRegions] = {kCompactTile, 16384, 512, 512, 16384, 256};
+  // particles per tile of each region's user; up to 2^18 particles the float64 pair
+  // pass, and up to 2^17 the emission, takes tiles of 256.  The emission is not what
+  // reserves: it may be given a descriptor with more slots than its push was, so its
+  // regions hold the tiles (512 emitters or more) of about twice as many particles,
+  // and a million more
+  const int64_t tile[kScanRegions] = {kCompactTile, 256, 256, 256, 16384, 256};
   int64_t words = 0;
   for (int k = 0; k < kScanRegions; ++k) {
     c->region_at[k] = words;
-    c->region_len[k] = n / tile[k] + 64 + (k == kRegEmit || k == kRegClean ? 2048 : 0);
+    c->region_len[k] = n / tile[k] + 64 + (k <= kRegEmitCont ? 2048 : 0);
     words += c->region_len[k];
   }
   if ((e = dalloc(&c->d_status, words)) != hipSuccess ||
