@@ -371,6 +371,7 @@ int qed_gather_push(qed_ctx_t c, const qed_fields_t *f, qed_species_t *lep, int 
   if (e != hipSuccess) return hip_fail(c, e, "gather_push");
   c->em_owner = lep->x;
   c->em_dtype = lep->dtype;
+  c->em_slots = lep->capacity;
   c->em_dt = dt;
   return QED_OK;
 }

@@ -29,7 +29,8 @@ constexpr int64_t kEmitSmall = (int64_t)1 << 17;
 // Uses of the scan state.  kRegClean: compaction and the float64 pair pass, whose
 // kernels leave it clear; the others are cleared by an earlier kernel of the same
 // call sequence: the emission's by qed_gather_push (its index's again by the first
-// surrogate pass), the float32 pair pass's by its streaming kernel.
+// surrogate pass; by a launch of their own if the emission is given another capacity),
+// the float32 pair pass's by its streaming kernel.
 enum ScanRegion { kRegClean = 0, kRegEmitIndex, kRegEmit, kRegEmitCont, kRegPairIndex, kRegPairCand, kScanRegions };
 
 struct qed_ctx {
@@ -66,6 +67,7 @@ struct qed_ctx {
   int64_t *d_n_emit = nullptr;
   const void *em_owner = nullptr;   // species (x pointer) the list belongs to
   int em_dtype = -1;
+  int64_t em_slots = 0;             // capacity that push was given (sizes what it cleared)
   int em_charge = 0;
   double em_dt = 0.0;
 

@@ -2405,6 +2405,8 @@ __global__ __launch_bounds__(kCThreads) void k_compact(SpeciesDev sp, ScanDev sc
 // ================================================================ misc
 __global__ void k_set_i64(int64_t *p, int64_t v) { *p = v; }
 
+__global__ __launch_bounds__(256) void k_scan_clear(ScanClear c) { scan_clear<256>(c); }
+
 __global__ void k_zero_scan(uint32_t *ticket, uint64_t *status, int64_t n) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i == 0) *ticket = 0;
@@ -2639,6 +2641,16 @@ static hipError_t clear_region(const qed_ctx *c, ScanClear &cl, int at, int k, i
   return hipSuccess;
 }
 
+// The scan regions of an emission for this many slots (index tiles of at least 16384
+// particles, emission tiles of at least 512 emitters, of 256 particles in a small
+// species).
+static hipError_t emit_clear(const qed_ctx *c, int64_t cap, bool use_mlp, ScanClear &clear) {
+  hipError_t e = clear_region(c, clear, 0, kRegEmitIndex, cap / ei_tile<1>() + 1);
+  if (e == hipSuccess) e = clear_region(c, clear, 1, kRegEmit, cap / (cap <= kEmitSmall ? kESTile : 512) + 1);
+  if (e == hipSuccess && use_mlp) e = clear_region(c, clear, 2, kRegEmitCont, cap / 512 + 1);
+  return e;
+}
+
 // Blocks of a gather/push launch for a species of this capacity, IT particles
 // per thread: every tile has its block (chunks per XCD, times the chunk, times
 // the 8 XCDs).
@@ -2722,13 +2734,8 @@ hipError_t launch_gather_push(qed_ctx *c, const qed_fields_t *f, const qed_speci
   const int64_t *dstep = step < 0 ? c->d_step : nullptr;
   const int64_t cap = sp->capacity;
   const bool use_mlp = (c->params.flags & QED_FLAG_SURROGATE) && sp->dtype == QED_F32;
-  // the scan regions of the emission that follows (index tiles of at least 16384
-  // particles, emission tiles of at least 512 emitters, of 256 particles in a small
-  // species)
-  ScanClear clear{};
-  hipError_t e = clear_region(c, clear, 0, kRegEmitIndex, cap / ei_tile<1>() + 1);
-  if (e == hipSuccess) e = clear_region(c, clear, 1, kRegEmit, cap / (cap <= kEmitSmall ? kESTile : 512) + 1);
-  if (e == hipSuccess && use_mlp) e = clear_region(c, clear, 2, kRegEmitCont, cap / 512 + 1);
+  ScanClear clear{};   // for the emission that follows
+  hipError_t e = emit_clear(c, cap, use_mlp, clear);
   if (e != hipSuccess) return e;
   if (use_mlp) {
     // surrogate path: the same pass with the rate envelope (thinning); the
@@ -2775,6 +2782,15 @@ hipError_t launch_emit(qed_ctx *c, const qed_species_t *lep, const qed_species_t
   const ScanDev isc = scan_region(c, kRegEmitIndex), sc = scan_region(c, kRegEmit);   // cleared by k_gather_push
   const int64_t *dstep = step < 0 ? c->d_step : nullptr;
   const int recoil = (c->params.flags & QED_FLAG_NO_RECOIL) ? 0 : 1;
+  if (lep->capacity != c->em_slots) {
+    // another descriptor of the arrays than the push's: its tiles are other ones, and
+    // words that the push left alone may hold an earlier call's sums
+    ScanClear clear{};
+    hipError_t e = emit_clear(c, lep->capacity, use_mlp, clear);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_scan_clear, dim3(64), dim3(256), 0, st, clear);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   // up to kEmitSmall particles the tables' emission takes its emitters from the
   // mask words themselves; above, a list gives every lane an emitter
   if (!use_mlp && lep->capacity <= kEmitSmall) {

@@ -72,3 +72,26 @@ def test_emission_with_more_slots_than_the_push_reserved(dtype, surrogate):
         ctx.close()
     assert out[0][2]["photons"] > 1000
     _same(out[0], out[1], dtype)
+
+
+@pytest.mark.parametrize("dtype,surrogate", [("f32", False), ("f64", False), ("f32", True)])
+@pytest.mark.parametrize("push,emit", [((1 << 17) + 1, 1 << 17), (1 << 17, (1 << 17) + 1), (1 << 17, 1 << 20)])
+def test_emission_with_other_slots_than_the_push(dtype, surrogate, push, emit):
+    """After calls that left the scan state of every tile behind: the capacity chooses
+    the tiles (256 particles up to 2^17, else 512 emitters or more), so what the push
+    clears for its own is not what the emission needs."""
+    torch, q = need_gpu()
+    n = 1 << 17
+    fld = q.Fields(q.QED_FIELD_UNIFORM, B=(0, 0, 2000.0))
+    out = []
+    for caps in ((push, emit), (emit, emit)):
+        print(f"emission: {dtype} surrogate={surrogate} slots {caps}", flush=True)
+        ctx = _context(q, surrogate)
+        lep, ph = _electrons(q, ctx, n, max(push, emit), dtype), q.Species(12 * n, dtype)
+        for s, (a, b) in enumerate([(emit, emit), (push, push), caps, caps]):
+            ctx.qed_gather_push(fld, _with_capacity(lep, a), -1, 0.02, s)
+            ctx.qed_emit_photons(_with_capacity(lep, b), ph, s)
+        out.append((ph.to_numpy(), lep.to_numpy(), ctx.qed_get_status()[0]))
+        ctx.close()
+    assert out[0][2]["photons"] > 10_000 and out[0][2]["dropped"] == 0
+    _same(out[0], out[1], dtype)
