@@ -151,6 +151,51 @@ __device__ __forceinline__ void gather_global(const FieldDev &f, const int j[3],
   }
 }
 
+// The same sums in the same order, with a row of the stencil (three nodes along x) read
+// while the one before is summed, held so by the scheduling barriers.  Left to itself
+// the compiler, short of registers, reads one node, waits for it and goes on, 27 times.
+// Particles in no cell order, whose boxes never fit: lepton pass of 5e6 on 128^3 1.71 ->
+// 1.22 ms, photon pass of 2e7 on 128^3 6.08 -> 5.06; intervals in which many boxes stop
+// fitting: table cascade of 5e6 on 128^3 14.3 -> 12.8 ms.  18 more registers hold reads
+// in flight; the two-particle lepton pass does not have them (it spills: 2e7 on 64^3,
+// sorted, 0.37 -> 0.54 ms).
+template <typename R>
+__device__ __forceinline__ void gather_global_rows(const FieldDev &f, const int j[3], const R w[3][3], R F[6]) {
+  const uint32_t sy6 = (uint32_t)f.nx * 6u, sz6 = sy6 * (uint32_t)f.ny;
+  uint32_t ox[3], oy[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    ox[a] = (uint32_t)wrap_index(j[0] + a - 1, f.nx) * 6u;
+    oy[a] = (uint32_t)wrap_index(j[1] + a - 1, f.ny) * sy6;
+  }
+#pragma unroll
+  for (int c = 0; c < 6; ++c) F[c] = (R)0;
+  float2 v[2][3][3];
+  auto load_row = [&](int buf, int r) {
+    const uint32_t row = (uint32_t)wrap_index(j[2] + r / 3 - 1, f.nz) * sz6 + oy[r % 3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const float2 *p2 = reinterpret_cast<const float2 *>(f.grid + (row + ox[a]));
+      v[buf][a][0] = p2[0]; v[buf][a][1] = p2[1]; v[buf][a][2] = p2[2];
+    }
+  };
+  load_row(0, 0);
+#pragma unroll
+  for (int r = 0; r < 9; ++r) {
+    if (r + 1 < 9) load_row((r + 1) & 1, r + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    const R wyz = w[1][r % 3] * w[2][r / 3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const R wt = w[0][a] * wyz;
+      const float2 *u = v[r & 1][a];
+      F[0] += wt * (R)u[0].x; F[1] += wt * (R)u[0].y; F[2] += wt * (R)u[1].x;
+      F[3] += wt * (R)u[1].y; F[4] += wt * (R)u[2].x; F[5] += wt * (R)u[2].y;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 template <typename R>
 __device__ __forceinline__ void gather_grid(const FieldDev &f, R x, R y, R z, R F[6]) {
   int j[3];
@@ -785,7 +830,10 @@ __global__ __launch_bounds__(T, (gp_waves<R, FK, M1>())) void k_gather_push(GPAr
     if (stage_box<1, T>(box_s, f, &live, j, rel, pit)) {   // its barriers also publish lnh_s
       if (live) gather_box<R, true>(box_s, rel[0], pit, w, F);
     } else {
-      if (live) gather_global<R>(f, j[0], w, F);
+      if (live) {
+        if constexpr (sizeof(R) == 4) gather_global_rows<R>(f, j[0], w, F);
+        else gather_global<R>(f, j[0], w, F);
+      }
       if (threadIdx.x == 0) atomicAdd(&counter_slot(a.counters)[cBoxFallback], 1ull);
     }
   } else {
@@ -2209,7 +2257,7 @@ __global__ __launch_bounds__(kGPThreads, Loop ? 4 : 5) void k_photon_grid(PairAr
     if (stage_box<1, T>(box_s, f, &present, j, rel, pit)) {   // its barriers also publish L_s and cnt_s
       if (alive) gather_box<float>(box_s, rel[0], pit, w, F);
     } else {
-      if (alive) gather_global<float>(f, j[0], w, F);
+      if (alive) gather_global_rows<float>(f, j[0], w, F);
     }
     bool ev = false;
     if (alive) {
