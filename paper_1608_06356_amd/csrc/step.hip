@@ -2199,17 +2199,17 @@ __global__ __launch_bounds__(kPTThreads, 4) void k_photon_table(PairArgs<float> 
 // the box of their stencils in LDS as the lepton pass does (stage_box); one whose
 // box is too large gathers from global memory, which cost every photon 27 scattered
 // reads.  Tiles are dealt to the XCDs in chunks (gp_tile_base).  One photon per
-// thread: two share a box but need 128 registers.  Five waves per SIMD (six take 66
-// registers and lose where boxes fall back).  Intervals of the table cascade: 3e6
-// electrons on 32^3 6.29 -> 4.61 ms, 1e7 on 64^3 18.9 -> 13.5, 5e6 on 128^3 16.5 ->
-// 13.6, 1e5 on 32^3 1.60 -> 1.33 (there one photon per thread counts, not four).
+// thread: two share a box but need 128 registers.  Bounded to five waves per SIMD, it
+// runs with six.  Intervals of the table cascade: 3e6 electrons on 32^3 6.29 -> 4.29 ms,
+// 1e7 on 64^3 18.9 -> 12.2, 5e6 on 128^3 16.5 -> 12.6, 1e5 on 32^3 1.90 -> 1.24.
 // Loop: a workgroup takes every kPhotonGroups-th tile (whole rounds of the dealing).
 // Photon species are made for many more photons than they hold, and a workgroup for
-// each tile of the capacity took 2 ms to find 1.2e9 slots empty.  The loop needs four
-// waves per SIMD: the interval of 3e6 electrons takes 4.4 ms either way, of 1e7 on
-// 64^3 12.6 against 12.7, of 5e6 on 128^3 14.3 against 13.5; up to kPhotonGroups tiles
-// there is none (1e5 electrons: 1.23 ms, with it 1.27).
-constexpr int64_t kPhotonGroups = 16 * kXcds * kGPChunk;
+// each tile of the capacity takes 0.2 ns a tile's worth of empty slots: a pass over 1e6
+// photons in 1.5e7 slots 49 us (with the loop 45), in 6e7 87 (46), in 1e9 860 (46).  The
+// loop has four waves per SIMD, which costs passes that hold what they were made for: 3e6
+// photons in no order 0.60 -> 0.64 ms, the interval of 5e6 electrons on 128^3 (1.5e7
+// slots) 12.6 -> 12.9; of 1e7 on 64^3 (3e7 slots) 12.2 either way.  Hence from 2^24 slots.
+constexpr int64_t kPhotonGroups = 16 * kXcds * kGPChunk, kPhotonLoopFrom = (int64_t)1 << 24;
 template <bool Thin, bool Loop>
 __global__ __launch_bounds__(kGPThreads, Loop ? 4 : 5) void k_photon_grid(PairArgs<float> a, uint64_t *emask, ScanClear clear) {
   constexpr int T = kGPThreads;
@@ -2954,7 +2954,7 @@ hipError_t launch_pairs(qed_ctx *c, const qed_fields_t *f, const qed_species_t *
     const int64_t ttiles = (ph->capacity + kPTTile - 1) / kPTTile, twgs = (int64_t)c->n_cu * 8;
     const dim3 tgrid((unsigned)(ttiles < twgs ? ttiles : twgs));
     const int64_t pgroups = gp_grid(ph->capacity, kGPThreads);
-    const bool loop = pgroups > kPhotonGroups;
+    const bool loop = ph->capacity >= kPhotonLoopFrom;
     auto pg = loop ? (thin ? k_photon_grid<true, true> : k_photon_grid<false, true>)
                    : (thin ? k_photon_grid<true, false> : k_photon_grid<false, false>);
     if (thin && a.ret.on)

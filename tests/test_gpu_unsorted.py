@@ -77,3 +77,48 @@ def test_lepton_pass_box_equals_rows(n, capacity, tile, surrogate):
     assert np.max(np.abs(a[0] - b[0])) <= 2.0 ** -20
     assert np.max(np.abs(a[1] - b[1]) / np.maximum(np.abs(b[1]), a0 * dt)) <= 2.0 ** -19
     np.testing.assert_allclose(a[2], b[2], rtol=1e-6, atol=1e-6)
+
+
+@pytest.mark.parametrize("surrogate", [False, True])
+@pytest.mark.parametrize("order", ["sorted", "random"])
+@pytest.mark.parametrize("n", [0, 1, 257, 4096 * 256 + 300])
+def test_photon_pass_in_rounds_of_workgroups(n, order, surrogate):
+    """A photon species with 2^24 slots, whose workgroups take more than one tile (4096
+    tiles a round), and one with a slot less: equal ids and pairs, positions bit for
+    bit, optical depths to the rounding of a float32 rate (two compilations: 64 units
+    in the last place of W dt <= tau's scale of 1).  Every third photon dead."""
+    torch, q = need_gpu()
+    ng, L, dt = 64, workloads.BOX_L, 0.01
+    rng = np.random.default_rng(n + 2)
+    x = rng.uniform(0.0, L, (n, 3))
+    k = rng.normal(size=(n, 3))
+    k *= (10.0 ** rng.uniform(0.0, 4.0, n) / np.linalg.norm(k, axis=1))[:, None]
+    tau, ids = rng.exponential(size=n) * 0.05, np.arange(n, dtype=np.uint64)
+    if order == "sorted":
+        cell = np.floor(x / (L / ng) + 0.5).astype(np.int64) % ng
+        c = [*cell.T, *(cell // 4).T]
+        key = np.lexsort(c)
+        x, k, tau = x[key], k[key], tau[key]
+    if n > 1000:
+        fit = _fitting(x, ng, L, 256)
+        assert fit > 0.5 if order == "sorted" else fit == 0
+    ids[1::3] = np.uint64(0xFFFFFFFFFFFFFFFF)
+    grid = torch.empty(ng ** 3 * 6, dtype=torch.float32, device="cuda")
+    fld = q.Fields(q.QED_FIELD_GRID, grid=grid, n=ng, L=L)
+    out = []
+    for cap in ((1 << 24) - 1, 1 << 24):
+        print(f"photon pass: n={n} {order} surrogate={surrogate} capacity {cap}", flush=True)
+        ctx = _context(q, surrogate)
+        ctx.qed_fill_standing_wave(grid, ng, L, 1000.0, 0.3)
+        ph, el, po = q.Species(cap, "f32"), q.Species(n + 1, "f32"), q.Species(n + 1, "f32")
+        ph.load(x, k, tau, ids)
+        ctx.qed_set_next_id(n)
+        ctx.qed_create_pairs(fld, ph, el, po, dt, 0)
+        out.append((ph.to_numpy(), el.to_numpy(), ctx.qed_get_status()[0]))
+        ctx.close()
+    (pa, ea, sa), (pb, eb, sb) = out
+    assert sa == sb and (n < 1000 or sa["pairs"] > 0)
+    for u, v in ((pa, pb), (ea, eb)):
+        assert np.array_equal(u["id"], v["id"])
+    assert np.array_equal(pa["x"], pb["x"])
+    assert np.all(np.abs(pa["tau"] - pb["tau"]) <= 64 * 2.0 ** -24 * np.maximum(1.0, np.abs(pa["tau"])))
