@@ -115,3 +115,17 @@ def test_tables_at_the_ends_of_the_range(formula, lnh_tol, s_tol, rad_hi, pair_h
     for i in (0, 255):
         assert np.abs(PS[i] - pref.s[i]).max() < 1e-8
     ctx.close()
+
+
+@pytest.mark.parametrize("rad_hi", [1.0, 1e6])
+def test_classical_table_at_the_ends_of_the_range(rad_hi):
+    """The same for Eq. 5, whose tail integral of K_{5/3} has a series of its own."""
+    torch, q = need_gpu()
+    ctx = q.Context()
+    ctx.qed_build_tables_range(q.QED_FORMULA_CLASSICAL, rad_hi, 10.0)
+    lnh, S = ctx.qed_get_table(0), ctx.qed_get_table(1)
+    ref = tables.build_rad_table("classical", rows=[0, 1, 255], chi_max=rad_hi)
+    for i in (0, 1, 255):
+        assert abs(lnh[i] - ref.ln_h[i]) < 1e-11
+        assert np.abs(S[i] - ref.s[i]).max() < 1e-8
+    ctx.close()
