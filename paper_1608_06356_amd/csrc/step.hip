@@ -158,7 +158,8 @@ __device__ __forceinline__ void gather_global(const FieldDev &f, const int j[3],
 // 1.22 ms, photon pass of 2e7 on 128^3 6.08 -> 5.06; intervals in which many boxes stop
 // fitting: table cascade of 5e6 on 128^3 14.3 -> 12.8 ms.  18 more registers hold reads
 // in flight; the two-particle lepton pass does not have them (it spills: 2e7 on 64^3,
-// sorted, 0.37 -> 0.54 ms).
+// sorted, 0.37 -> 0.54 ms), and method I's, with few waves, loses (1e6 on 32^3 in no
+// order 132 -> 147 us).
 template <typename R>
 __device__ __forceinline__ void gather_global_rows(const FieldDev &f, const int j[3], const R w[3][3], R F[6]) {
   const uint32_t sy6 = (uint32_t)f.nx * 6u, sz6 = sy6 * (uint32_t)f.ny;
@@ -831,7 +832,7 @@ __global__ __launch_bounds__(T, (gp_waves<R, FK, M1>())) void k_gather_push(GPAr
       if (live) gather_box<R, true>(box_s, rel[0], pit, w, F);
     } else {
       if (live) {
-        if constexpr (sizeof(R) == 4) gather_global_rows<R>(f, j[0], w, F);
+        if constexpr (sizeof(R) == 4 && !M1) gather_global_rows<R>(f, j[0], w, F);
         else gather_global<R>(f, j[0], w, F);
       }
       if (threadIdx.x == 0) atomicAdd(&counter_slot(a.counters)[cBoxFallback], 1ull);
