@@ -485,7 +485,9 @@ __device__ __forceinline__ void count_flags(unsigned long long *c, int which, bo
 // kernels below draw no more than they need: the workgroups past the tiles present
 // leave without one, and where every tile has its own workgroup no one draws a
 // second (single_turn).  Before, 1024 workgroups drew two each whatever the work:
-// 17 of 30 us of an emission with 190 tiles.
+// 17 of 30 us of an emission with 190 tiles.  The launchers keep the workgroups to those
+// that are on the chip at once, since one that has to wait for another's end starts
+// later than that other would draw its tile.
 __device__ __forceinline__ bool idle_block(int64_t ntiles) { return (int64_t)blockIdx.x >= ntiles; }
 __device__ __forceinline__ bool single_turn(int64_t ntiles) { return ntiles <= (int64_t)gridDim.x; }
 
@@ -1125,7 +1127,8 @@ __device__ void emit_tile(const EmitArgs<R> &a, const Tab &tab, const R *lnh, ui
 // an event, one event after the other for the emitters with several; the launches
 // saved are most of the call.  Push and emission of 24000 float32 electrons take
 // 19 us a step (33 with a list and two clearing launches), of 1e5 float64 ones 27
-// (37).
+// (37).  Two waves per SIMD at least: method I in float64 takes two registers too many
+// for them by itself (131072 electrons 38 us instead of 32).
 constexpr int kESTile = 256, kESWords = kESTile / 64;
 
 template <typename R> struct EmitTab;
@@ -1159,7 +1162,7 @@ __device__ __forceinline__ bool tile_emitter(const uint64_t m[kESWords], int r, 
 }
 
 template <typename R, bool M1>
-__global__ __launch_bounds__(kESTile) void k_emit_small(EmitArgs<R> a, const uint64_t *mask) {
+__global__ __launch_bounds__(kESTile, 2) void k_emit_small(EmitArgs<R> a, const uint64_t *mask) {
   __shared__ R lnh_s[kRadNChi];
   __shared__ uint64_t scan_s[16], off_s;
   __shared__ uint32_t tile_s, cnt_s[cNumCounters];
@@ -2882,9 +2885,10 @@ hipError_t launch_emit(qed_ctx *c, const qed_species_t *lep, const qed_species_t
                        c->em_idx, c->d_n_emit, isc, c->d_counters);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // persistent workgroups: one per CU for the surrogate (its nets fill the LDS),
-  // up to four per CU otherwise
-  const int64_t wgs = use_mlp ? (int64_t)c->n_cu : 4 * (int64_t)c->n_cu;
+  // persistent workgroups, one per CU: the surrogate's nets fill the LDS, the others
+  // the registers (method I, all of 131073 float32 electrons emitting, 257 tiles: 87 us,
+  // 96 with a workgroup per tile)
+  const int64_t wgs = c->n_cu;
   const unsigned grid = (unsigned)(ntiles < wgs ? ntiles : wgs);
   if (use_mlp) {
     EmitArgs<float> a = emit_args<float>(c, lep, ph, step, recoil, sc);
@@ -2982,7 +2986,7 @@ hipError_t launch_pairs(qed_ctx *c, const qed_fields_t *f, const qed_species_t *
     else
       hipLaunchKernelGGL((k_emit_index<1, int32_t>), dim3(eig), dim3(kEIThreads), 0, st, c->cand_mask, ph->count,
                          c->cand_idx, c->d_n_cand, isc, c->d_counters);
-    const int64_t ewgs = (int64_t)c->n_cu * 4;
+    const int64_t ewgs = (int64_t)c->n_cu * (thin ? 2 : 4);   // (k_pair_cand: two on a CU at once)
     const dim3 egrid((unsigned)(ctiles < ewgs ? ctiles : ewgs));
     if (thin) {
       hipLaunchKernelGGL(k_pair_cand, egrid, dim3(kPCThreads), 0, st, a, c->cand_idx, c->d_n_cand, c->mlp_theta[1],
