@@ -1717,10 +1717,14 @@ __device__ __forceinline__ bool photon_rate(const PairArgs<R> &a, const R *L, in
 // index through one scan of per-level counts packed 16 bits per level; pass 2
 // makes the (rare) events' pairs from the photon's stream (with several photons per
 // thread it evaluates chi again).  Four photons per thread where there are enough
-// of them to fill the GPU; one in a small species (kPairSmall), whose time is the
-// latency of a tile: a call takes 14 us with 2e4 photons (31 with four per thread),
-// 20 with 1e5 (34), 35 with 2.6e5 (35), 59 with four per thread and 1e6.
-constexpr int64_t kPairSmall = (int64_t)1 << 18;
+// of them to fill the GPU; fewer in a small species (kPairSmall slots), whose time is the
+// latency of a tile: one up to kPairOne photons, and on a grid, whose gather that latency
+// mostly is; else two, which leaves as many tiles as the chip holds workgroups.  A call
+// with one / two / four per thread, static photons in a uniform field, none converting:
+// 2e4 photons 18 / - / 23 us, 1.3e5 26 / - / 24, 1.6e5 28 / 23 / 24, 2.6e5 34 / 27 /
+// 25; some converting: 2.6e5 39 / 35 / 40; on a grid, some converting: 2e4 25 / - / 60,
+// 1.6e5 46 / 56 / 60, 2.6e5 54 / 58 / 62 (none 49 / 43 / 41).
+constexpr int64_t kPairSmall = (int64_t)1 << 18, kPairOne = (int64_t)1 << 17;
 
 template <int kPairItems, typename R, typename Tab>
 __device__ void pair_tile(const PairArgs<R> &a, const Tab &tab, const R *L, uint32_t tile,
@@ -2361,9 +2365,8 @@ __global__ void k_pair_commit(PairArgs<float> a, const int64_t *n_ev) {
   if (a.killed && tt) atomicAdd((unsigned long long *)a.killed, (unsigned long long)tt);
 }
 
-template <int Items>
+template <bool Small>
 __global__ __launch_bounds__(kPairThreads) void k_pairs_f64(PairArgs<double> a) {
-  constexpr int kPairTile = kPairThreads * Items;
   __shared__ double L_s[kPairNRate];
   __shared__ uint64_t scan_s[16];
   __shared__ uint32_t tile_s;
@@ -2378,14 +2381,17 @@ __global__ __launch_bounds__(kPairThreads) void k_pairs_f64(PairArgs<double> a) 
   __syncthreads();
   const int64_t n = hdr_s[0], e0 = hdr_s[1], p0 = hdr_s[2];
   const uint64_t id0 = (uint64_t)hdr_s[3];
-  const int64_t ntiles = (n + kPairTile - 1) / kPairTile;
+  const bool one = n <= kPairOne || a.f.kind == QED_FIELD_GRID;      // (small species)
+  const int64_t per = (Small ? (one ? 1 : 2) : 4) * kPairThreads, ntiles = (n + per - 1) / per;
   if (idle_block(ntiles)) return;
   for (int k = threadIdx.x; k < kPairNRate; k += blockDim.x) L_s[k] = a.L[k];
   const RowF64 tab{a.S64};
   while (true) {
     const uint32_t tile = next_tile_clean(a.sc, &tile_s, ntiles);
     if ((int64_t)tile >= ntiles) break;
-    pair_tile<Items, double>(a, tab, L_s, tile, scan_s, &off_s, n, e0, p0, id0, cnt_s);
+    if constexpr (!Small) pair_tile<4, double>(a, tab, L_s, tile, scan_s, &off_s, n, e0, p0, id0, cnt_s);
+    else if (one) pair_tile<1, double>(a, tab, L_s, tile, scan_s, &off_s, n, e0, p0, id0, cnt_s);
+    else pair_tile<2, double>(a, tab, L_s, tile, scan_s, &off_s, n, e0, p0, id0, cnt_s);
   }
   count_flush(cnt_s, a.counters);
   // retired photons are dead too: the compaction of this species must not skip
@@ -2941,7 +2947,7 @@ hipError_t launch_pairs(qed_ctx *c, const qed_fields_t *f, const qed_species_t *
   const ScanDev sc = scan_region(c, ph->dtype == QED_F32 ? kRegPairCand : kRegClean);
   if (ph->dtype != QED_F32 && ntiles > c->region_len[kRegClean]) return hipErrorInvalidValue;
   const int move = (c->params.flags & QED_FLAG_STATIC_PHOTONS) ? 0 : 1;
-  const int64_t wgs = (int64_t)c->n_cu * 4;   // persistent, tiles from the ticket
+  const int64_t wgs = (int64_t)c->n_cu * 2;   // as many as fit, tiles from the ticket
   const unsigned grid = (unsigned)(ntiles < wgs ? ntiles : wgs);
   // killed-photon count: known only if this species was compacted before
   int64_t *killed = ((c->params.flags & QED_FLAG_TRACK_DEAD) && c->killed_owner == ph->x) ? c->d_killed : nullptr;
@@ -3000,8 +3006,8 @@ hipError_t launch_pairs(qed_ctx *c, const qed_fields_t *f, const qed_species_t *
                        c->pair_S64, c->pair_q16, c->pair_s0sc, dt, dt, move, c->d_next_id,
                        c->params.seed, (uint64_t)step, step < 0 ? c->d_step : nullptr, sc, c->d_counters, killed, c->range,
                       retire_dev(c)};
-    if (small) hipLaunchKernelGGL(k_pairs_f64<1>, dim3(grid), dim3(kPairThreads), 0, st, a);
-    else hipLaunchKernelGGL(k_pairs_f64<4>, dim3(grid), dim3(kPairThreads), 0, st, a);
+    if (small) hipLaunchKernelGGL(k_pairs_f64<true>, dim3(grid), dim3(kPairThreads), 0, st, a);
+    else hipLaunchKernelGGL(k_pairs_f64<false>, dim3(grid), dim3(kPairThreads), 0, st, a);
   }
   return hipGetLastError();
 }

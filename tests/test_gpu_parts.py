@@ -59,3 +59,49 @@ def test_emission_whole_equals_parts(dtype, method1, dt):
     assert sa == sb and sa["photons"] == pa["id"].size > 1000 and sa["dropped"] == 0
     _same(la, lb, dtype)
     _same(pa, pb, dtype)
+
+
+@pytest.mark.parametrize("path", ["f64", "f32", "surrogate"])
+@pytest.mark.parametrize("grid", [False, True])
+@pytest.mark.parametrize("n,part", [(150_001, 1 << 16), ((1 << 18) - 1, 1 << 17), (300_001, 150_001), (300_001, 1 << 16)])
+def test_pairs_whole_equals_parts(path, grid, n, part):
+    """A third of the photons convert at once, the others have a step's time.  Float64: one
+    photon per thread up to 2^17 and on a grid, two up to 2^18 slots, four above;
+    surrogate: more tiles of candidates than the chip holds workgroups."""
+    torch, q = need_gpu()
+    dtype = "f64" if path == "f64" else "f32"
+    ng, L = 16, workloads.BOX_L
+    rng = np.random.default_rng(n)
+    x = rng.uniform(0.0, L, (n, 3))
+    k = rng.normal(size=(n, 3))
+    k *= (10.0 ** rng.uniform(2.0, 4.0, n) / np.linalg.norm(k, axis=1))[:, None]
+    tau, ids = rng.exponential(size=n) * 0.05, np.arange(n, dtype=np.uint64)
+    tau[::3] = 1e-6
+    gr = torch.empty(ng ** 3 * 6, dtype=torch.float32, device="cuda")
+    out = []
+    for size in (n, part):
+        print(f"pairs: {path} grid={grid} n={n} in parts of {size}", flush=True)
+        ctx = q.Context(seed=2, kmax=4, flags=q.QED_FLAG_SURROGATE if path == "surrogate" else 0)
+        ctx.qed_build_tables(q.QED_FORMULA_I)
+        if path == "surrogate":             # (weights of any kind: a rate outside the envelope takes the table)
+            for net in (0, 1):
+                m = q.lib().qed_surrogate_params(net)
+                ctx.qed_surrogate_io(net, np.random.default_rng(net).normal(0, 0.05, m).astype(np.float32))
+        ctx.qed_fill_standing_wave(gr, ng, L, 2000.0, 0.3)
+        fld = (q.Fields(q.QED_FIELD_GRID, grid=gr, n=ng, L=L) if grid
+               else q.Fields(q.QED_FIELD_UNIFORM, E=(100.0, -50.0, 30.0), B=(0, 0, 2000.0)))
+        ctx.qed_set_next_id(n)
+        el, po, phs = q.Species(n, dtype), q.Species(n, dtype), []
+        for a in range(0, n, size):
+            b = min(a + size, n)
+            ph = q.Species(b - a, dtype)
+            ph.load(x[a:b], k[a:b], tau[a:b], ids[a:b])
+            ctx.qed_create_pairs(fld, ph, el, po, 0.01, 0)
+            phs.append(ph)
+        st, _ = ctx.qed_get_status()
+        out.append(([_join([s.to_numpy() for s in phs]), el.to_numpy(), po.to_numpy()], st))
+        ctx.close()
+    (a, sa), (b, sb) = out
+    assert sa == sb and sa["pairs"] == a[1]["id"].size > n // 20 and sa["dropped"] == 0
+    for u, v in zip(a, b):
+        _same(u, v, dtype)
