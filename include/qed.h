@@ -169,8 +169,8 @@ QED_API void qed_destroy(qed_ctx_t ctx);
 QED_API const char *qed_last_error(qed_ctx_t ctx);
 
 /* Reserves the context's scan state for species of up to `max_particles`
-   elements and its emitter list (one 128-byte record slot, one mask bit and one
-   list entry per lepton) for lepton species of up to `max_particles` (allocates;
+   elements and its emitter list (one 128-byte record slot, three mask bits and two
+   list entries per lepton) for lepton species of up to `max_particles` (allocates;
    call before graph capture).  Without it, or when a species is larger, the
    entry points grow what they need on first use: the scan state in every entry
    point that appends or compacts, the emitter list in qed_gather_push for the
@@ -251,7 +251,9 @@ QED_API int qed_gather_push(qed_ctx_t ctx, const qed_fields_t *fields, qed_speci
    again within the step (at most kmax events).  Photons are appended after
    photons->count in (emitter index, k) order; with QED_FLAG_SURROGATE (float32)
    the first events of all emitters come first, in emitter order, then the later
-   events of the emitters that have them, in (emitter index, k) order. */
+   events of the emitters that have them, in (emitter index, k) order.
+   `leptons` may be a descriptor with another capacity than the one qed_gather_push was
+   given, if both hold the particles present (that takes one more launch). */
 QED_API int qed_emit_photons(qed_ctx_t ctx, qed_species_t *leptons, qed_species_t *photons,
                      int64_t step, void *stream);
 

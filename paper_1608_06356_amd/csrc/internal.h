@@ -59,7 +59,8 @@ struct qed_ctx {
   // emitter list produced by qed_gather_push
   int64_t reserved = 0;          // species size the scan state covers
   int64_t em_cap = 0;            // emitter slots (one per lepton of the largest lepton species)
-  uint64_t *em_mask = nullptr;   // one bit per particle: optical depth ran out this step
+  uint64_t *em_mask = nullptr;   // one bit per particle: optical depth ran out this step; then two masks over
+                                 // the list (surrogate emission: photon accepted, photon stored)
   EmIdx *em_idx = nullptr;       // ordered emitter list
   unsigned char *em_rec = nullptr;   // em_cap records of up to kEmRecMaxBytes, slot = particle index
   int32_t *cont_idx = nullptr;   // surrogate emission: emitters with a further candidate (list positions)
@@ -85,7 +86,7 @@ struct qed_ctx {
   const void *killed_owner = nullptr;
 
   // decoupled look-back scan state: a ticket and a region of status words for each
-  // use (ScanRegion), all clear between calls
+  // use (ScanRegion, which says when each is clear)
   uint32_t *d_ticket = nullptr;
   uint64_t *d_status = nullptr;
   int64_t region_at[kScanRegions] = {}, region_len[kScanRegions] = {};

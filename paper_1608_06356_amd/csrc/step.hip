@@ -306,8 +306,8 @@ __device__ __forceinline__ bool stage_box(BoxLds<T> &S, const FieldDev &f, const
   if ((int64_t)pxy * bdim[2] > S.kCap) return false;
   // copy the box: node p of the dense enumeration (x fastest) -> (x, y, z).
   // The quotients use the hardware reciprocal (relative error below 2^-22):
-  // (p + 0.5) / d is at least 0.5 / d <= 2^-11 away from an integer and below
-  // 2^11, so the truncation is exact.
+  // (p + 0.5) / d is at least 0.5 / d away from an integer, and p + 0.5 below 2^11
+  // makes its error at most 2^-11 / d, so the truncation is exact.
   const int bxy = bdim[0] * bdim[1], cnt = bxy * bdim[2];
   const float inv_bx = __builtin_amdgcn_rcpf((float)bdim[0]), inv_bxy = __builtin_amdgcn_rcpf((float)bxy);
   int g0[3];
@@ -1866,7 +1866,8 @@ __device__ void pair_tile(const PairArgs<R> &a, const Tab &tab, const R *L, uint
 // not change within the step), up to kmax candidates.  Counter k of the photon's
 // PHOTON_THIN stream gives (keep draw, new optical depth) of candidate k; a kept
 // candidate makes the pair exactly as pair_tile does (PHOTON_EVENT, counter 0).
-// Three launches: k_photon_thin moves every photon, runs its optical depth down
+// Three launches: k_photon_thin (on a grid without the field bound k_photon_grid) moves
+// every photon, runs its optical depth down
 // at W_env and marks the candidates in a ballot mask (the other photons'
 // optical depths are final there); k_emit_index lists the candidates in photon
 // order; k_pair_cand takes them one per lane, so that the net runs on full
@@ -2021,11 +2022,11 @@ __global__ __launch_bounds__(kPCThreads) void k_pair_cand(PairArgs<float> a, con
     if (valid) {
       pid = a.ph.id[i];
       kx = KX[i]; ky = KY[i]; kz = KZ[i];
-      x = X[i]; y = Y[i]; z = Z[i];                 // moved by k_photon_thin
+      x = X[i]; y = Y[i]; z = Z[i];                 // moved by the photon pass
       tau = a.ph.tau[i];                            // the optical depth before the step
       gph = root<float>(kx * kx + ky * ky + kz * kz);
       field_at<float>(a.f, i, x, y, z, F);
-      // (without the field bound k_photon_thin counted these already)
+      // (without the field bound the photon pass counted these already)
       if (fields_finite<float>(F)) {
         chi = chi_photon_f32(kx, ky, kz, F);
         if (isfinite(chi)) {
@@ -2037,7 +2038,9 @@ __global__ __launch_bounds__(kPCThreads) void k_pair_cand(PairArgs<float> a, con
       } else {
         nnan += a.ret.on;
       }
-      We = photon_envelope(a, chi, gph);           // the envelope k_photon_thin used
+      // the envelope the photon pass used (k_photon_grid's own compilation of the field
+      // and of |k| to rounding: a time left that comes out negative by it ends the step)
+      We = photon_envelope(a, chi, gph);
     }
     // with the local envelope the first keep draw below the squeeze keeps the
     // candidate without the net; otherwise the pair head gives W
