@@ -861,7 +861,8 @@ constexpr int64_t kDenseGP = 64;
 // on 128^3).  A re-sort interval of 12 steps with 256 / 512 threads: 5e6 electrons
 // on 128^3 (2.4 per cell) 3.34 / 3.09 ms, 2e6 on 96^3 (2.3) 1.60 / 1.52, of 15
 // steps 1e7 on 128^3 (4.8) 6.19 / 6.06; above, the boxes fit and the larger
-// workgroup's barriers cost more: 5e6 on 96^3 (5.7) 2.36 / 2.50.
+// workgroup's barriers cost more: 5e6 on 96^3 (5.7) 2.36 / 2.50.  (They cost sparse
+// species some of the gain right after a sort: 5e6 on 128^3 122 / 126 us a pass.)
 constexpr int64_t kSparseGP = 5, kSparseMin = (int64_t)1 << 19;
 template <bool Thin>
 __global__ __launch_bounds__(kGPThreads, kGPWaves) void k_gather_push2(GPArgs<float> a) {
@@ -2405,7 +2406,9 @@ __global__ __launch_bounds__(kPairThreads) void k_pairs_f64(PairArgs<double> a) 
 // ============================================================== compact
 constexpr int kCThreads = 256, kCItems = 4, kCTile = kCThreads * kCItems;
 
-template <typename R>
+// Clean: the scan state is left clear (next_tile_clean); otherwise its caller clears it
+// before each call (the static one, which calls of several contexts share).
+template <typename R, bool Clean>
 __global__ __launch_bounds__(kCThreads) void k_compact(SpeciesDev sp, ScanDev sc,
                                                        unsigned long long *counters, int64_t *killed) {
   __shared__ uint32_t scan_s[16];
@@ -2414,22 +2417,28 @@ __global__ __launch_bounds__(kCThreads) void k_compact(SpeciesDev sp, ScanDev sc
   // killed: particles marked dead since the last compaction of this species, when
   // known (pair creation keeps it); nothing to do if none
   if (killed && *killed == 0) return;
-  // (the count and `killed` change only once every workgroup has read them, when
-  // the last ticket of all is drawn)
+  // (Clean: the count and `killed` change only once every workgroup has read them, when
+  // the last ticket of all is drawn.  Otherwise they change with the last tile: every
+  // tile has been drawn then, so a workgroup that starts later and reads the new count
+  // finds none)
   const int64_t n = *sp.count, ntiles = (n + kCTile - 1) / kCTile;
   if (idle_block(ntiles) && (ntiles > 0 || blockIdx.x > 0)) return;
   R *A[6] = {(R *)sp.x, (R *)sp.y, (R *)sp.z, (R *)sp.px, (R *)sp.py, (R *)sp.pz};
+  auto finish = [&](int64_t nn) {
+    if (nn < n) {
+      atomicAdd(&counters[cCompacted], (unsigned long long)(n - nn));
+      *sp.count = nn;
+    }
+    if (killed) *killed = 0;
+  };
   while (true) {
-    const uint32_t tile = next_tile_clean(sc, &tile_s, ntiles, [&] {
-      if (n) {
-        const int64_t nn = (int64_t)(ld_status(&sc.status[ntiles - 1]) & kValMask);
-        if (nn < n) {
-          atomicAdd(&counters[cCompacted], (unsigned long long)(n - nn));
-          *sp.count = nn;
-        }
-      }
-      if (killed) *killed = 0;
-    });
+    uint32_t tile;
+    if constexpr (Clean)
+      tile = next_tile_clean(sc, &tile_s, ntiles,
+                             [&] { finish(n ? (int64_t)(ld_status(&sc.status[ntiles - 1]) & kValMask) : 0); });
+    else
+      tile = next_tile(sc.ticket, &tile_s);
+    if (!Clean && n == 0 && threadIdx.x == 0) finish(0);
     const int64_t base = (int64_t)tile * kCTile;
     if (base >= n) break;
     R v[kCItems][6];
@@ -2465,6 +2474,10 @@ __global__ __launch_bounds__(kCThreads) void k_compact(SpeciesDev sp, ScanDev sc
         sp.id[r] = id[it];
         ++r;
       }
+    }
+    if constexpr (!Clean) {
+      if ((int64_t)tile == ntiles - 1 && threadIdx.x == 0) finish((int64_t)(toff + total));
+      if (single_turn(ntiles)) break;
     }
   }
 }
@@ -3012,12 +3025,13 @@ hipError_t launch_pairs(qed_ctx *c, const qed_fields_t *f, const qed_species_t *
   return hipGetLastError();
 }
 
-static hipError_t launch_compact_at(qed_ctx *c, const qed_species_t *sp, const ScanDev &sc, hipStream_t st);
+static hipError_t launch_compact_at(qed_ctx *c, const qed_species_t *sp, const ScanDev &sc, bool clean,
+                                    hipStream_t st);
 
 hipError_t launch_compact(qed_ctx *c, const qed_species_t *sp, hipStream_t st) {
   const ScanDev sc = scan_region(c, kRegClean);
   if ((sp->capacity + kCTile - 1) / kCTile > c->region_len[kRegClean]) return hipErrorInvalidValue;
-  return launch_compact_at(c, sp, sc, st);
+  return launch_compact_at(c, sp, sc, true, st);
 }
 
 static_assert(kCTile == kCompactTile, "compaction tile size of the scan-state bound");
@@ -3026,10 +3040,11 @@ hipError_t launch_compact_scan(qed_ctx *c, const qed_species_t *sp, uint32_t *ti
                                int64_t status_len, hipStream_t st) {
   const int64_t ntiles = (sp->capacity + kCTile - 1) / kCTile;
   hipError_t e = zero_scan_at(ticket, status, status_len, ntiles, st);
-  return e == hipSuccess ? launch_compact_at(c, sp, ScanDev{ticket, status}, st) : e;
+  return e == hipSuccess ? launch_compact_at(c, sp, ScanDev{ticket, status}, false, st) : e;
 }
 
-static hipError_t launch_compact_at(qed_ctx *c, const qed_species_t *sp, const ScanDev &sc, hipStream_t st) {
+static hipError_t launch_compact_at(qed_ctx *c, const qed_species_t *sp, const ScanDev &sc, bool clean,
+                                    hipStream_t st) {
   const int64_t ntiles = (sp->capacity + kCTile - 1) / kCTile;
   hipError_t e = hipSuccess;
   const bool track = (c->params.flags & QED_FLAG_TRACK_DEAD) != 0;
@@ -3039,12 +3054,9 @@ static hipError_t launch_compact_at(qed_ctx *c, const qed_species_t *sp, const S
   // all return at once
   const int64_t wgs = (int64_t)c->n_cu * 8;
   const unsigned grid = (unsigned)(ntiles < wgs ? ntiles : wgs);
-  if (sp->dtype == QED_F32)
-    hipLaunchKernelGGL(k_compact<float>, dim3(grid), dim3(kCThreads), 0, st, dev_species(sp), sc, c->d_counters,
-                       killed);
-  else
-    hipLaunchKernelGGL(k_compact<double>, dim3(grid), dim3(kCThreads), 0, st, dev_species(sp), sc,
-                       c->d_counters, killed);
+  auto k = sp->dtype == QED_F32 ? (clean ? k_compact<float, true> : k_compact<float, false>)
+                                : (clean ? k_compact<double, true> : k_compact<double, false>);
+  hipLaunchKernelGGL(k, dim3(grid), dim3(kCThreads), 0, st, dev_species(sp), sc, c->d_counters, killed);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // the species now has no dead particles (the kernel clears the count of the
   // species it tracks already)
