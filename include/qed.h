@@ -101,7 +101,7 @@ typedef struct qed_ctx *qed_ctx_t;
 
 typedef struct {
   uint32_t seed;      /* xor-ed into the Philox key                                  */
-  int32_t  kmax;      /* max events per lepton per step, 1..8 (cap is counted)       */
+  int32_t  kmax;      /* max events per lepton per step, 1..4 (cap is counted)       */
   uint32_t flags;     /* QED_FLAG_*                                                  */
   int32_t  reserved;
 } qed_params_t;
